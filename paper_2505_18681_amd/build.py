@@ -54,6 +54,9 @@ UNITS = [
 ] + [
     ("seg_block.hip", f"seg_block_k{kb}_v{vb}.o", [f"-DEVOSORT_KB={kb}", f"-DEVOSORT_VB={vb}"])
     for kb in (4, 8) for vb in (0, 4, 8)
+] + [
+    ("radix_runs.hip", f"radix_runs_k{kb}_v{vb}.o", [f"-DEVOSORT_KB={kb}", f"-DEVOSORT_VB={vb}"])
+    for kb in (8,) for vb in (0, 4, 8)
 ]
 
 

@@ -143,6 +143,7 @@ constexpr uint32_t kDefaultSpinLimit = 1u << 24;
 constexpr uint32_t kDefaultInsertion = 8;
 constexpr size_t kAlign = 256;
 constexpr int64_t kStatus32Limit = (int64_t)1 << 30;  // 32-bit look-back words hold counts < 2^30
+constexpr int64_t kPrefixMinKeys = (int64_t)1 << 14;  // fewer keys: no prefix sort is considered
 constexpr uint64_t kPrefixMinTiles = 256;  // fewer tiles: pass 0 uses the look-back
 
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
@@ -269,7 +270,8 @@ struct Plan {
     uint32_t t_ins;
     // radix scratch layout (byte offsets into temp)
     size_t off_keys_a, off_keys_b, off_vals, off_hist, off_bases, off_status, off_ctr, off_err, off_blocks, off_live,
-        off_done;
+        off_done, off_plan, off_sample, off_long;
+    bool prefix_sort;  // a prefix sort may be chosen (SampleArgs, PrefixChoice)
     bool prefix0;  // pass 0 takes its tile offsets from the histogram's per-tile counts
     size_t zero_begin, zero_end;
     size_t status_pass_bytes;
@@ -422,7 +424,10 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
         P->off_err = 0;
         P->off_live = 16;  // the live-pass word (zeroed here, bits set by the scan)
         P->off_done = 20;  // scan workgroups finished
+        P->off_plan = 24;  // the scan's plan word
         P->off_ctr = 64;   // 64-bit ticket counters: passes * 8 <= 128 bytes
+        P->off_sample = 192;  // sample counts (kSampleWords words)
+        P->off_long = 232;    // long runs listed
         off = kAlign;
         P->off_hist = off;
         off = align_up(off + (size_t)passes * bins * 8);
@@ -439,7 +444,10 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
         // the look-back is cheaper (int32, ms per sort with / without:
         // 1e5 0.124 / 0.105, 1e6 0.162 / 0.132, 3e6 (163 tiles) 0.204 /
         // 0.175, 1e7 (543 tiles) 0.301 / 0.307).
-        P->prefix0 = P->bits == 8 && passes == kb && tiles >= kPrefixMinTiles;
+        // 8-byte keys: the passes of the lower digits are left out when the
+        // upper digits already tell the keys apart (see prefix_choice).
+        P->prefix_sort = P->bits == 8 && kb == 8 && n >= kPrefixMinKeys;
+        P->prefix0 = P->bits == 8 && passes == kb && tiles >= kPrefixMinTiles && !P->prefix_sort;
         P->off_blocks = off;
         if (P->prefix0)
             off = align_up(off + (size_t)((tiles + kTilePrefixBlock - 1) / kTilePrefixBlock) * 256 * 8);
@@ -532,6 +540,35 @@ namespace {
 unsigned char* at(void* temp, size_t off) { return reinterpret_cast<unsigned char*>(temp) + off; }
 
 // ------------------------------------------------------------ radix path ----
+// The sample a prefix sort is chosen from: one group of kSampleKeys keys per
+// 250 000 keys (1 to 1024), which resolves runs of kRunMean keys on average in any
+// array.  With runs of L keys a group of S keys holds about S * S * L / (2 n)
+// neighbours that the prefix does not tell apart.
+constexpr int64_t kRunMean = 4;
+SampleArgs prefix_sample(int64_t n, uint32_t* counts)
+{
+    SampleArgs sa{};
+    const int64_t groups = n / 250000;
+    sa.groups = (uint32_t)(groups < 1 ? 1 : (groups > 1024 ? 1024 : groups));
+    // Heavy: a key with more than some 4096 copies in the array; seen with
+    // fewer copies in a group where there are many groups to see it in.
+    // Huge: more than some 131072 copies, with a margin for the luck of the
+    // draw (one workgroup sorts 131072 keys in about 1.5 ms).
+    const int64_t copies = (4096 * (int64_t)kSampleKeys + n - 1) / n, least = groups >= 64 ? 3 : 4;
+    sa.heavy_copies = (uint32_t)(copies < least ? least : copies);
+    sa.huge_copies = (uint32_t)(sa.heavy_copies + 3 * (131072 * (int64_t)kSampleKeys / n));
+    sa.counts = counts;
+    return sa;
+}
+PrefixChoice prefix_choice(int64_t n, const SampleArgs& sa, bool in_place)
+{
+    PrefixChoice c{};
+    c.sample = sa.counts;
+    c.most_pairs = (uint32_t)((int64_t)sa.groups * kSampleKeys * kSampleKeys * kRunMean / (2 * n));
+    c.even_stages = in_place;
+    return c;
+}
+
 // Buffers: the input keys (read only unless sorted in place), the output, and
 // one (argsort: two) key buffer(s) in temp; values likewise.  Every pass is
 // launched; on the device each pass learns from the scan which passes have a
@@ -553,6 +590,23 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
     auto* live = reinterpret_cast<uint32_t*>(at(temp, P.off_live));
     auto* done = reinterpret_cast<uint32_t*>(at(temp, P.off_done));
 
+    auto* plan = reinterpret_cast<uint32_t*>(at(temp, P.off_plan));
+    const bool argsort = P.op == EVOSORT_OP_ARGSORT;
+    const bool pairs = P.op == EVOSORT_OP_SORT_PAIRS;
+    // sorted in place: the first live pass must not write the output it reads
+    const bool in_place = !argsort && (keys_out == keys_in || (pairs && vals_out == vals_in));
+    ScanArgs scan{};
+    scan.bases = bases;
+    scan.live = live;
+    scan.done = done;
+    scan.tickets = tickets;
+    scan.plan = plan;
+    SampleArgs sample{};
+    if (P.prefix_sort) {
+        sample = prefix_sample(n, reinterpret_cast<uint32_t*>(at(temp, P.off_sample)));
+        scan.prefix = prefix_choice(n, sample, in_place);
+    }
+
     EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(at(temp, P.zero_begin), P.zero_end - P.zero_begin, s));
     if (P.prefix0) {
         void* counts0 = at(temp, P.off_status);  // pass 0's status words hold its tile prefixes
@@ -563,18 +617,16 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
                        launch_tile_prefix(counts0, (int)P.info.status_bytes, (uint32_t)P.info.tiles,
                                           reinterpret_cast<uint64_t*>(at(temp, P.off_blocks)), s));
     } else {
-        EVOSORT_LAUNCH("radix_histogram", s, launch_radix_histogram(P.kd, keys_in, n, P.bits, passes, hist, s));
+        EVOSORT_LAUNCH("radix_histogram", s,
+                       launch_radix_histogram(P.kd, keys_in, n, P.bits, passes, hist, sample, s));
     }
-    EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, bases, P.bits, passes, live, done, tickets, s));
+    EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, P.bits, passes, scan, s));
 
-    const bool argsort = P.op == EVOSORT_OP_ARGSORT;
-    const bool pairs = P.op == EVOSORT_OP_SORT_PAIRS;
     RadixRoute r{};
-    r.live = live;
+    r.plan = plan;
     r.passes = (uint32_t)passes;
     r.flags = argsort ? ROUTE_ARGSORT : 0u;
-    // sorted in place: the first live pass must not write the output it reads
-    if (!argsort && (keys_out == keys_in || (pairs && vals_out == vals_in)))
+    if (in_place)
         r.flags |= ROUTE_COPY_IF_ODD;
     r.keys_in = keys_in;
     r.keys_out = argsort ? nullptr : keys_out;
@@ -605,6 +657,23 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
         EVOSORT_LAUNCH("radix_pass", s,
                        launch_radix_pass(P.kd, vb, P.bits, P.shape, (int)P.info.status_bytes, a,
                                          (uint32_t)P.info.tiles, s));
+    }
+    if (P.prefix_sort) {
+        // The list of long runs and the tiles' marks go where pass 0's
+        // look-back words are, zeroed with them.  A prefix sort always leaves
+        // pass 0 out (two live passes are below its first one, one when that
+        // was moved down by one for an even number of stages), and a tile of
+        // at most 20480 keys has 1 KB of words, more than 8 bytes per kRunMost
+        // and 4 per kRunTile keys.
+        RadixRunArgs ra{};
+        ra.route = r;
+        ra.n = n;
+        ra.long_count = reinterpret_cast<uint32_t*>(at(temp, P.off_long));
+        ra.long_runs = reinterpret_cast<int64_t*>(at(temp, P.off_status));
+        ra.unsorted = reinterpret_cast<uint32_t*>(at(temp, P.off_status + (size_t)(n / kRunMost + 1) * 8));
+        EVOSORT_LAUNCH("radix_runs", s, launch_radix_runs(P.kd, vb, ra, s));
+        EVOSORT_LAUNCH("radix_long_runs", s, launch_radix_long_runs(P.kd, vb, ra, s));
+        return EVOSORT_OK;
     }
     EVOSORT_LAUNCH("radix_finish", s, launch_radix_finish(r, n, kb, vb, s));
     return EVOSORT_OK;
@@ -1187,10 +1256,12 @@ evosort_status evosort_radix_histogram(int dtype, const void* keys, int64_t n, u
     // hist_out is zeroed and filled directly (row_bytes is a multiple of 16)
     EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(hist_out, row_bytes, s));
     if (n > 0)
-        EVOSORT_LAUNCH("radix_histogram", s, launch_radix_histogram(kd, keys, n, bits, passes, hist_out, s));
-    if (bases_out)
-        EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist_out, bases_out, bits, passes, nullptr, nullptr, nullptr,
-                                                          s));
+        EVOSORT_LAUNCH("radix_histogram", s, launch_radix_histogram(kd, keys, n, bits, passes, hist_out, SampleArgs{}, s));
+    if (bases_out) {
+        ScanArgs sa{};
+        sa.bases = bases_out;
+        EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist_out, bits, passes, sa, s));
+    }
     return EVOSORT_OK;
 }
 
@@ -1228,9 +1299,10 @@ evosort_status evosort_radix_pass(int dtype, const void* keys_in, void* keys_out
     auto* bases = reinterpret_cast<uint64_t*>(at(temp, P.off_bases));
     EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(at(temp, P.zero_begin), P.zero_end - P.zero_begin, s));
     EVOSORT_LAUNCH("radix_histogram", s,
-                   launch_radix_histogram(P.kd, keys_in, n, P.bits, (int)P.info.passes, hist, s));
-    EVOSORT_LAUNCH("radix_scan", s,
-                   launch_radix_scan(hist, bases, P.bits, (int)P.info.passes, nullptr, nullptr, nullptr, s));
+                   launch_radix_histogram(P.kd, keys_in, n, P.bits, (int)P.info.passes, hist, SampleArgs{}, s));
+    ScanArgs sa{};
+    sa.bases = bases;
+    EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, P.bits, (int)P.info.passes, sa, s));
     RadixPassArgs a{};
     a.keys_in = keys_in;
     a.keys_out = keys_out;

@@ -21,8 +21,35 @@ struct KeyDesc {
 // One read of the keys: histograms of every digit position, added into
 // hist[passes << bits] (uint64, zeroed by the caller).  When all passes do not
 // fit in LDS at once the passes are split over several launches.
+// With 8-bit digits in one launch, `sample` (when its groups are not 0) also
+// draws a sample of the keys for the choice of a prefix sort (SampleArgs).
+struct SampleArgs {
+    uint32_t groups = 0;         // sampling workgroups of kSampleKeys keys each (0: none)
+    uint32_t heavy_copies = 0;   // copies of one key in a group's sample that make it a heavy key, and
+    uint32_t huge_copies = 0;    // a huge one
+    uint32_t* counts = nullptr;  // kSampleWords zeroed words: neighbours by highest differing byte, then SAMPLE_*
+};
+constexpr int kSampleKeys = 1024;       // keys per sampling workgroup
+constexpr uint32_t kSampleWords = 10;
+constexpr uint32_t SAMPLE_NEAR = 8;     // 8 - the lowest of the highest bytes in which a heavy key and a neighbour differ
+constexpr uint32_t SAMPLE_HEAVY = 9;    // 1: there is a heavy key, 2: a huge one
+// What a prefix sort is chosen by (radix_scan_kernel).
+struct PrefixChoice {
+    const uint32_t* sample = nullptr;  // SampleArgs::counts; null: no prefix sort
+    uint32_t most_pairs = 0;           // sampled neighbours of one prefix that the choice accepts
+    bool even_stages = false;          // sorted in place: an odd number of stages would end in the scratch
+};
+// Where the scan of a routed sort puts its results (launch_radix_scan).
+struct ScanArgs {
+    uint64_t* bases = nullptr;
+    uint32_t* live = nullptr;               // one zeroed word
+    uint32_t* done = nullptr;               // one zeroed word
+    unsigned long long* tickets = nullptr;  // passes zeroed words
+    uint32_t* plan = nullptr;
+    PrefixChoice prefix;
+};
 hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n, int bits, int passes,
-                                  uint64_t* hist, hipStream_t s);
+                                  uint64_t* hist, const SampleArgs& sample, hipStream_t s);
 
 // The all-pass histogram of 8-bit digits (passes 4 or 8, zeroed hist) that
 // also writes, for every tile of tile_keys keys, the tile's counts of the
@@ -43,9 +70,20 @@ constexpr uint32_t kTilePrefixBlock = 64;  // tiles per workgroup of the prefix 
 // every key would leave the order unchanged.
 // `done` (one zeroed word) and `tickets` (passes 64-bit ticket counters,
 // zeroed) go with `live`: the last scan workgroup writes each pass's route
-// code (route_code below) into the upper half of that pass's ticket counter.
-hipError_t launch_radix_scan(const uint64_t* hist, uint64_t* bases, int bits, int passes, uint32_t* live,
-                             uint32_t* done, unsigned long long* tickets, hipStream_t s);
+// code (route_code below) into the upper half of that pass's ticket counter,
+// and the whole sort's plan word (plan_word below) to *plan.  With
+// prefix.sample it may choose a prefix sort from the sample's counts.  Without
+// `live` only the bases are written.
+hipError_t launch_radix_scan(const uint64_t* hist, int bits, int passes, const ScanArgs& a, hipStream_t s);
+
+// The plan of a routed sort: its number of stages m (live passes, plus one for
+// the run sort of a prefix sort) and the first pass of a prefix sort (0: none).
+__host__ __device__ constexpr uint32_t plan_word(uint32_t stages, uint32_t prefix_pass)
+{
+    return stages | (prefix_pass << 8);
+}
+__host__ __device__ constexpr uint32_t plan_stages(uint32_t plan) { return plan & 0xffu; }
+__host__ __device__ constexpr uint32_t plan_prefix_pass(uint32_t plan) { return (plan >> 8) & 0xffu; }
 
 // Route code of a pass in the upper half of its ticket counter: routed, live,
 // its index j among the live passes and their number m.
@@ -61,7 +99,8 @@ __host__ __device__ constexpr uint32_t route_m(uint32_t code) { return (code >> 
 // Buffers of a whole radix sort, from which each pass picks its input and
 // output on the device once the live passes are known (the scan's `live`
 // word): the launch sequence stays the same whatever digits are constant.
-// Live pass j (0-based among the m live passes) reads what live pass j - 1
+// The m stages are the live passes, plus the run sort of a prefix sort as the
+// last one.  Stage j (0-based among the m stages; below "live pass") reads what live pass j - 1
 // wrote (the input for j = 0) and writes
 //   keys-only / pairs:  the output when m - 1 - j is even, else the
 //                       temporary buffer; with ROUTE_COPY_IF_ODD (sorting in
@@ -74,7 +113,7 @@ __host__ __device__ constexpr uint32_t route_m(uint32_t code) { return (code >> 
 // With no live pass the finishing launch copies the input to the output
 // (argsort: writes the identity permutation).
 struct RadixRoute {
-    const uint32_t* live;  // the scan's live-pass word (read by the finishing launch); null: no routing
+    const uint32_t* plan;  // the scan's plan word (read by the run sort and the finishing launch)
     uint32_t pass, passes;
     uint32_t flags;        // ROUTE_*
     const void* keys_in;
@@ -130,6 +169,28 @@ bool radix_pass_available(int key_bytes, int val_bytes, int bits, RadixShape sha
 hipError_t launch_radix_finish(const RadixRoute& r, int64_t n, int key_bytes, int val_bytes, hipStream_t s);
 hipError_t launch_radix_pass(const KeyDesc& kd, int val_bytes, int bits, RadixShape shape, int status_bytes,
                              const RadixPassArgs& a, uint32_t tiles, hipStream_t s);
+
+// ------------------------------------------------- runs of a prefix sort ----
+// A prefix sort runs only the passes of the upper digits, which leaves keys
+// with equal upper digits (a run) beside each other in input order; one last
+// stage sorts every run by the lower digits.  When the upper digits already
+// tell almost all keys apart the runs are short, and that stage replaces all
+// the lower passes (radix_runs.hip).
+constexpr int kRunMost = 256;  // longest run sorted by rank counting; longer ones are listed
+constexpr int kRunTile = 4096;  // keys per workgroup step of the run sort
+
+struct RadixRunArgs {
+    RadixRoute route;
+    int64_t n;
+    uint32_t* long_count;  // zeroed
+    int64_t* long_runs;    // first key of every listed run: room for n / kRunMost entries
+    uint32_t* unsorted;    // per tile of kRunTile keys, zeroed: a key of a listed run is above the next one
+};
+// The run sort; when the plan holds no prefix sort, the copy that
+// launch_radix_finish would make (this launch replaces it).
+hipError_t launch_radix_runs(const KeyDesc& kd, int val_bytes, const RadixRunArgs& a, hipStream_t s);
+// After launch_radix_runs: the listed runs out of order, one workgroup each.
+hipError_t launch_radix_long_runs(const KeyDesc& kd, int val_bytes, const RadixRunArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- misc -----
 

@@ -1,5 +1,6 @@
 // Launchers of the radix histogram and scan kernels, the utility kernels, and
 // the dispatch of the pass kernel over (key bytes, value bytes).
+#include "radix_finish.hpp"
 #include "radix_impl.hpp"
 #include "radix_shapes.hpp"
 
@@ -25,6 +26,13 @@ hipError_t seg_pass_dispatch_k8_v0(RadixShape, const KeyDesc&, const SegPassArgs
 hipError_t seg_pass_dispatch_k8_v4(RadixShape, const KeyDesc&, const SegPassArgs&, uint32_t, hipStream_t, bool*);
 hipError_t seg_pass_dispatch_k8_v8(RadixShape, const KeyDesc&, const SegPassArgs&, uint32_t, hipStream_t, bool*);
 
+hipError_t radix_runs_k8_v0(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+hipError_t radix_long_runs_k8_v0(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+hipError_t radix_runs_k8_v4(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+hipError_t radix_long_runs_k8_v4(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+hipError_t radix_runs_k8_v8(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+hipError_t radix_long_runs_k8_v8(const KeyDesc&, const RadixRunArgs&, hipStream_t);
+
 // Compute units of the MI355X (gfx950) the size-dependent grids and tiles are
 // chosen for.
 constexpr int64_t kComputeUnits = 256;
@@ -47,12 +55,17 @@ int histogram_grid(int64_t n)
         want = 4096;
     if (n <= (int64_t)1 << 23 && want > kComputeUnits)
         want = kComputeUnits;
+    // up to 2^27 keys three per CU (1e7 int64 keys: the whole sort 364 us with
+    // 768, 384 with 256, 396 with 2441 workgroups; 2e8 keys 6.33 ms with 768,
+    // 6.30 with 4096)
+    if (n <= (int64_t)1 << 27 && want > 3 * kComputeUnits)
+        want = 3 * kComputeUnits;
     return (int)want;
 }
 }  // namespace
 
 hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n, int bits, int passes,
-                                  uint64_t* hist, hipStream_t s)
+                                  uint64_t* hist, const SampleArgs& sample, hipStream_t s)
 {
     // LDS budget of one launch: 64 KB of 32-bit counters.  Group the passes so
     // that each group has at least one private copy; add copies (at most one
@@ -61,20 +74,24 @@ hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n
     if (bits == 8 && (passes == 4 || passes == 8)) {
         // every pass in one launch, one set of counters per workgroup (as in
         // launch_radix_histogram_tiles)
-        const int grid = histogram_grid(n);
+        const int grid = histogram_grid(n) + (int)sample.groups;
         const int copies = 1;
-        const size_t lds = (size_t)copies * passes * per_pass;
+        size_t lds = (size_t)copies * passes * per_pass;
+        if (sample.groups && lds < (size_t)kSampleKeys * kd.bytes)
+            lds = (size_t)kSampleKeys * kd.bytes;
         auto* h = reinterpret_cast<unsigned long long*>(hist);
         if (kd.bytes == 4 && passes == 4) {
             OrderMap<uint32_t> om{(uint32_t)kd.flip, (uint32_t)kd.neg, (uint32_t)kd.desc};
             hipLaunchKernelGGL((radix_histogram8_kernel<4, kHistThreads, 4>), dim3(grid), dim3(kHistThreads), lds,
-                               s, reinterpret_cast<const uint32_t*>(keys), n, om, copies, h);
+                               s, reinterpret_cast<const uint32_t*>(keys), n, om, copies, h,
+                               sample);
             return hipGetLastError();
         }
         if (kd.bytes == 8 && passes == 8) {
             OrderMap<uint64_t> om{kd.flip, kd.neg, kd.desc};
             hipLaunchKernelGGL((radix_histogram8_kernel<8, kHistThreads, 8>), dim3(grid), dim3(kHistThreads), lds,
-                               s, reinterpret_cast<const uint64_t*>(keys), n, om, copies, h);
+                               s, reinterpret_cast<const uint64_t*>(keys), n, om, copies, h,
+                               sample);
             return hipGetLastError();
         }
     }
@@ -177,11 +194,9 @@ hipError_t launch_tile_prefix(void* counts, int status_bytes, uint32_t tiles, ui
     return hipGetLastError();
 }
 
-hipError_t launch_radix_scan(const uint64_t* hist, uint64_t* bases, int bits, int passes, uint32_t* live,
-                             uint32_t* done, unsigned long long* tickets, hipStream_t s)
+hipError_t launch_radix_scan(const uint64_t* hist, int bits, int passes, const ScanArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((radix_scan_kernel<256>), dim3(passes), dim3(256), 0, s, hist, bases, 1 << bits, live, done,
-                       tickets);
+    hipLaunchKernelGGL((radix_scan_kernel<256>), dim3(passes), dim3(256), 0, s, hist, 1 << bits, a);
     return hipGetLastError();
 }
 
@@ -408,43 +423,6 @@ uint32_t stream_grid(size_t bytes)
     return (uint32_t)g;
 }
 
-// bytes is a multiple of 4 (keys, values and indices are 4 or 8 bytes).
-__device__ __forceinline__ void copy_range(unsigned char* __restrict__ dst, const unsigned char* __restrict__ src,
-                                           size_t bytes, size_t tid, size_t nthreads)
-{
-    size_t done = 0;
-    if (((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15) == 0) {
-        const size_t n16 = bytes / 16;
-        uint4* d = reinterpret_cast<uint4*>(dst);
-        const uint4* s = reinterpret_cast<const uint4*>(src);
-        size_t i = tid;
-        // eight 16-byte words in flight per thread
-        for (; i + 7 * nthreads < n16; i += 8 * nthreads) {
-            const uint4 w0 = s[i], w1 = s[i + nthreads], w2 = s[i + 2 * nthreads], w3 = s[i + 3 * nthreads];
-            const uint4 w4 = s[i + 4 * nthreads], w5 = s[i + 5 * nthreads], w6 = s[i + 6 * nthreads],
-                        w7 = s[i + 7 * nthreads];
-            // every load is issued before the first store: the scheduler
-            // would otherwise pair each load with its store and wait on each
-            __builtin_amdgcn_sched_barrier(0);
-            d[i] = w0;
-            d[i + nthreads] = w1;
-            d[i + 2 * nthreads] = w2;
-            d[i + 3 * nthreads] = w3;
-            d[i + 4 * nthreads] = w4;
-            d[i + 5 * nthreads] = w5;
-            d[i + 6 * nthreads] = w6;
-            d[i + 7 * nthreads] = w7;
-        }
-        for (; i < n16; i += nthreads)
-            d[i] = s[i];
-        done = n16 * 16;
-    }
-    uint32_t* d4 = reinterpret_cast<uint32_t*>(dst + done);
-    const uint32_t* s4 = reinterpret_cast<const uint32_t*>(src + done);
-    for (size_t i = tid; i < (bytes - done) / 4; i += nthreads)
-        d4[i] = s4[i];
-}
-
 __global__ __launch_bounds__(kStreamThreads) void stream_copy_kernel(unsigned char* dst, const unsigned char* src,
                                                                      size_t bytes)
 {
@@ -490,51 +468,41 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s)
     return hipGetLastError();
 }
 
-// After the passes of a routed sort (see RadixRoute): with no live pass, the
-// input goes to the output unchanged (argsort: the identity permutation);
-// with an odd number of live passes sorted in place, the last pass's
-// temporary buffer goes to the output; otherwise every workgroup leaves.
 __global__ __launch_bounds__(kStreamThreads) void radix_finish_kernel(RadixRoute r, int64_t n, int kb, int vb)
 {
-    const uint32_t m = (uint32_t)__builtin_popcount(*r.live);
-    const size_t tid = (size_t)blockIdx.x * kStreamThreads + threadIdx.x;
-    const size_t nth = (size_t)gridDim.x * kStreamThreads;
-    const bool argsort = (r.flags & ROUTE_ARGSORT) != 0;
-    if (m == 0) {
-        if (argsort) {
-            if (vb == 4) {
-                for (size_t i = tid; i < (size_t)n; i += nth)
-                    reinterpret_cast<uint32_t*>(r.vals_out)[i] = (uint32_t)i;
-            } else {
-                for (size_t i = tid; i < (size_t)n; i += nth)
-                    reinterpret_cast<uint64_t*>(r.vals_out)[i] = (uint64_t)i;
-            }
-            return;
-        }
-        if (r.keys_out != r.keys_in)
-            copy_range(reinterpret_cast<unsigned char*>(r.keys_out), reinterpret_cast<const unsigned char*>(r.keys_in),
-                       (size_t)n * kb, tid, nth);
-        if (vb && r.vals_out != r.vals_in)
-            copy_range(reinterpret_cast<unsigned char*>(r.vals_out), reinterpret_cast<const unsigned char*>(r.vals_in),
-                       (size_t)n * vb, tid, nth);
-        return;
-    }
-    if (!argsort && (r.flags & ROUTE_COPY_IF_ODD) && (m & 1)) {
-        copy_range(reinterpret_cast<unsigned char*>(r.keys_out), reinterpret_cast<const unsigned char*>(r.keys_tmp),
-                   (size_t)n * kb, tid, nth);
-        if (vb)
-            copy_range(reinterpret_cast<unsigned char*>(r.vals_out), reinterpret_cast<const unsigned char*>(r.vals_tmp),
-                       (size_t)n * vb, tid, nth);
-    }
+    finish_copies(r, plan_stages(*r.plan), n, kb, vb, (size_t)blockIdx.x * kStreamThreads + threadIdx.x,
+                  (size_t)gridDim.x * kStreamThreads);
 }
 
 hipError_t launch_radix_finish(const RadixRoute& r, int64_t n, int key_bytes, int val_bytes, hipStream_t s)
 {
-    if (n <= 0 || !r.live)
+    if (n <= 0 || !r.plan)
         return hipSuccess;
     hipLaunchKernelGGL(radix_finish_kernel, dim3(stream_grid((size_t)n * (key_bytes > val_bytes ? key_bytes : val_bytes))),
                        dim3(kStreamThreads), 0, s, r, n, key_bytes, val_bytes);
     return hipGetLastError();
+}
+
+hipError_t launch_radix_runs(const KeyDesc& kd, int val_bytes, const RadixRunArgs& a, hipStream_t s)
+{
+    if (a.n <= 0)
+        return hipSuccess;
+    if (kd.bytes != 8)
+        return hipErrorInvalidValue;
+    return val_bytes == 0   ? radix_runs_k8_v0(kd, a, s)
+           : val_bytes == 4 ? radix_runs_k8_v4(kd, a, s)
+                            : radix_runs_k8_v8(kd, a, s);
+}
+
+hipError_t launch_radix_long_runs(const KeyDesc& kd, int val_bytes, const RadixRunArgs& a, hipStream_t s)
+{
+    if (a.n <= 0)
+        return hipSuccess;
+    if (kd.bytes != 8)
+        return hipErrorInvalidValue;
+    return val_bytes == 0   ? radix_long_runs_k8_v0(kd, a, s)
+           : val_bytes == 4 ? radix_long_runs_k8_v4(kd, a, s)
+                            : radix_long_runs_k8_v8(kd, a, s);
 }
 
 hipError_t launch_stream_read(const void* src, size_t bytes, uint64_t* sink, hipStream_t s)

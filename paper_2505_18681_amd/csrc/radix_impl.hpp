@@ -96,6 +96,170 @@ __global__ __launch_bounds__(THREADS) void radix_histogram_kernel(const typename
     }
 }
 
+// One thread: the routes of a sort's passes and its plan, from the mask of the
+// passes whose digit takes more than one value.
+__device__ __forceinline__ void write_plan(uint32_t mask, uint32_t passes, const ScanArgs& a)
+{
+    // A prefix sort from pass p0 on: the highest p0 whose upper digits leave
+    // few sampled neighbours untold apart (runs of about kRunMean keys at
+    // most), provided it spares two live passes or more (the run sort costs
+    // about one pass).  A heavy key's run is long; it should hold nothing else,
+    // since one workgroup has to sort it otherwise: no sampled key may be as
+    // near to a heavy one as two digits above p0 (a stranger in the run is then
+    // some 65536 times less likely than one that the sample would show), and
+    // huge runs are left to the passes.
+    uint32_t p0 = 0;
+    if (a.prefix.sample) {
+        const uint32_t* sample = a.prefix.sample;
+        const uint32_t near = sample[SAMPLE_NEAR], heavy = sample[SAMPLE_HEAVY];
+        uint32_t untold = 0;
+        for (uint32_t q = 1; q + 1 < passes; ++q) {
+            untold += sample[q - 1];
+            if (untold <= a.prefix.most_pairs && (heavy == 0 || (heavy == 1 && near != 0 && q + 2 + near <= 8)))
+                p0 = q;
+        }
+        const uint32_t below = (1u << p0) - 1u;
+        if (__builtin_popcount(mask & below) < 2 || (mask & ~below) == 0)
+            p0 = 0;
+        // in place, an even number of stages: one more live pass instead of a copy
+        if (p0 && a.prefix.even_stages && (__builtin_popcount(mask >> p0) & 1) == 0)
+            p0 = 31u - (uint32_t)__builtin_clz(mask & below);
+        mask &= ~((1u << p0) - 1u);
+    }
+    const uint32_t m = (uint32_t)__builtin_popcount(mask) + (p0 ? 1u : 0u);
+    *a.plan = plan_word(m, p0);
+    for (uint32_t q = 0; q < passes; ++q) {
+        const uint32_t j = (uint32_t)__builtin_popcount(mask & ((1u << q) - 1u));
+        a.tickets[q] = (unsigned long long)route_code((mask >> q) & 1u, j, m) << 32;
+    }
+}
+
+// Bitonic steps of stride 2^(LG-1) and below among the 256 words a wave holds,
+// word 4 * lane + q in x[q]: `up` says for each lane and q whether the word's
+// block ascends.
+template <int LG, typename U>
+__device__ __forceinline__ void wave_bitonic_steps(U (&x)[4], int lane, uint32_t up_bits)
+{
+    if constexpr (LG >= 3) {
+        constexpr int M = 1 << (LG - 3);  // the partner's lane
+        const bool upper = (lane & M) != 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const U y = __shfl_xor(x[q], M, kWave);
+            const bool keep_small = upper != (((up_bits >> q) & 1) != 0);
+            x[q] = (y < x[q]) == keep_small ? y : x[q];
+        }
+        wave_bitonic_steps<LG - 1>(x, lane, up_bits);
+    } else if constexpr (LG >= 1) {
+        constexpr int M = 1 << (LG - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if ((q & M) == 0) {
+                const U a = x[q], b = x[q + M];
+                const bool swap = (b < a) == (((up_bits >> q) & 1) != 0);
+                x[q] = swap ? b : a;
+                x[q + M] = swap ? a : b;
+            }
+        }
+        wave_bitonic_steps<LG - 1>(x, lane, up_bits);
+    }
+}
+
+// One workgroup's sample of the keys, for the choice of a prefix sort:
+// kSampleKeys keys at jittered even spacing over the whole array (group g
+// takes the g-th part), sorted, and of every two neighbours in that order the
+// highest byte they differ in is counted.  The counts summed over bytes below
+// p are the neighbours that the digits from p on do not tell apart.  A key
+// with heavy_copies copies in the sample is heavy: its run is long whatever
+// the digits, and must hold nothing else (SAMPLE_* below).
+// Runs beside the counting workgroups of the histogram launch and is a chain
+// of 55 compare steps: all but three of them stay inside a wave (four keys per
+// lane), since as LDS steps with barriers they outlast the histogram of 1e5
+// keys by 10 us.
+template <int KB, int THREADS>
+__device__ void sample_keys(const typename KeyWord<KB>::U* __restrict__ keys, int64_t n,
+                            const OrderMap<typename KeyWord<KB>::U>& om, uint32_t group, const SampleArgs& sa,
+                            typename KeyWord<KB>::U* s, uint32_t* found)
+{
+    using U = typename KeyWord<KB>::U;
+    constexpr uint32_t S = kSampleKeys;
+    static_assert(S == 1024 && THREADS == 256, "four waves of 256 keys");
+    if (threadIdx.x < kSampleWords)
+        found[threadIdx.x] = 0;
+    const uint64_t total = (uint64_t)sa.groups * S;
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const uint32_t e0 = threadIdx.x * 4;  // words e0 .. e0 + 3 of the sample
+    U x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint64_t i = (uint64_t)group * S + e0 + q;
+        // i * n / total without leaving 64 bits (i < 2^20, n < 2^43)
+        const uint64_t lo = i * (uint64_t)n / total, hi = (i + 1) * (uint64_t)n / total;
+        const uint32_t h = (uint32_t)(i * 2654435761u) ^ (uint32_t)(i >> 3);
+        const uint64_t at = lo + (hi > lo + 1 ? (uint64_t)(h % (uint32_t)(hi - lo)) : 0);
+        x[q] = om.to_order(keys[at < (uint64_t)n ? at : (uint64_t)n - 1]);
+    }
+    // bit q: the block of 2^lg words that holds word e0 + q ascends
+    auto up_bits = [&](int lg) {
+        uint32_t b = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            b |= (((e0 + q) >> lg) & 1) ? 0u : 1u << q;
+        return b;
+    };
+    wave_bitonic_steps<1>(x, lane, up_bits(1));
+    wave_bitonic_steps<2>(x, lane, up_bits(2));
+    wave_bitonic_steps<3>(x, lane, up_bits(3));
+    wave_bitonic_steps<4>(x, lane, up_bits(4));
+    wave_bitonic_steps<5>(x, lane, up_bits(5));
+    wave_bitonic_steps<6>(x, lane, up_bits(6));
+    wave_bitonic_steps<7>(x, lane, up_bits(7));
+    wave_bitonic_steps<8>(x, lane, up_bits(8));
+    // blocks of 512 and 1024 words: strides of 256 and 512 through LDS
+#pragma unroll
+    for (int lg = 9; lg <= 10; ++lg) {
+        const uint32_t up = up_bits(lg);
+        for (uint32_t st = 1u << (lg - 1); st >= 256; st /= 2) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                s[e0 + q] = x[q];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const U y = s[(e0 + q) ^ st];
+                const bool keep_small = (((e0 + q) & st) != 0) != (((up >> q) & 1) != 0);
+                x[q] = (y < x[q]) == keep_small ? y : x[q];
+            }
+            __syncthreads();
+        }
+        wave_bitonic_steps<8>(x, lane, up);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        s[e0 + q] = x[q];
+    __syncthreads();
+    const uint32_t hc = sa.heavy_copies;  // >= 2
+    for (uint32_t i = threadIdx.x; i + 1 < S; i += THREADS) {
+        const U x = s[i] ^ s[i + 1];
+        if (x == 0) {
+            if (i + hc <= S && s[i] == s[i + hc - 1])
+                atomicMax(&found[SAMPLE_HEAVY], i + sa.huge_copies <= S && s[i] == s[i + sa.huge_copies - 1] ? 2u : 1u);
+            continue;
+        }
+        const uint32_t byte = (uint32_t)(63 - __clzll((long long)(uint64_t)x)) >> 3;
+        atomicAdd(&found[byte], 1u);
+        if ((i + 1 >= hc && s[i + 1 - hc] == s[i]) || (i + hc < S && s[i + hc] == s[i + 1]))
+            atomicMax(&found[SAMPLE_NEAR], 8u - byte);
+    }
+    __syncthreads();
+    if (threadIdx.x < kSampleWords && found[threadIdx.x]) {
+        if (threadIdx.x < SAMPLE_NEAR)
+            atomicAdd(&sa.counts[threadIdx.x], found[threadIdx.x]);
+        else
+            atomicMax(&sa.counts[threadIdx.x], found[threadIdx.x]);
+    }
+}
+
 // The same for 8-bit digits and all passes in one launch (the common case),
 // with the pass count known at compile time.  Skewed, presorted and sparse
 // keys: lds_count_passes lets one lane count the lanes that share lane 0's
@@ -103,12 +267,19 @@ __global__ __launch_bounds__(THREADS) void radix_histogram_kernel(const typename
 template <int KB, int THREADS, int PASSES>
 __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typename KeyWord<KB>::U* __restrict__ keys,
                                                                    int64_t n, OrderMap<typename KeyWord<KB>::U> om,
-                                                                   int copies, unsigned long long* __restrict__ hist)
+                                                                   int copies, unsigned long long* __restrict__ hist,
+                                                                   SampleArgs sample)
 {
     using U = typename KeyWord<KB>::U;
     constexpr int BINS = 256;
     constexpr int PER_COPY = PASSES * BINS;
     extern __shared__ uint32_t lds_hist[];
+    // the first workgroups sample, the others count
+    if (blockIdx.x < sample.groups) {
+        __shared__ uint32_t found[kSampleWords];
+        sample_keys<KB, THREADS>(keys, n, om, blockIdx.x, sample, reinterpret_cast<U*>(lds_hist), found);
+        return;
+    }
     for (int i = threadIdx.x; i < copies * PER_COPY; i += THREADS)
         lds_hist[i] = 0;
     __syncthreads();
@@ -121,8 +292,8 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typenam
 
     constexpr int VEC = 16 / KB;
     constexpr int UNROLL = 4;
-    const int64_t stride = (int64_t)gridDim.x * THREADS;
-    const int64_t gtid = (int64_t)blockIdx.x * THREADS + threadIdx.x;
+    const int64_t stride = (int64_t)(gridDim.x - sample.groups) * THREADS;
+    const int64_t gtid = (int64_t)(blockIdx.x - sample.groups) * THREADS + threadIdx.x;
     int64_t done = 0;
     if ((reinterpret_cast<uintptr_t>(keys) & 15) == 0) {
         const int64_t nvec = n / VEC;
@@ -358,17 +529,14 @@ __global__ __launch_bounds__(256) void tile_prefix_kernel(ST* __restrict__ count
 // unchanged: its pass can go)
 // ------------------------------------------------------------------------
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void radix_scan_kernel(const uint64_t* __restrict__ hist,
-                                                             uint64_t* __restrict__ bases, int bins,
-                                                             uint32_t* __restrict__ live, uint32_t* done,
-                                                             unsigned long long* tickets)
+__global__ __launch_bounds__(THREADS) void radix_scan_kernel(const uint64_t* __restrict__ hist, int bins, ScanArgs a)
 {
     __shared__ uint64_t part[THREADS];
     __shared__ uint32_t one_digit;
     if (threadIdx.x == 0)
         one_digit = 0;
     const uint64_t* row = hist + (size_t)blockIdx.x * bins;
-    uint64_t* out = bases + (size_t)blockIdx.x * bins;
+    uint64_t* out = a.bases + (size_t)blockIdx.x * bins;
     const int per = (bins + THREADS - 1) / THREADS;
     const int b0 = threadIdx.x * per;
     uint64_t s = 0;
@@ -395,23 +563,18 @@ __global__ __launch_bounds__(THREADS) void radix_scan_kernel(const uint64_t* __r
                 one_digit = 1;  // every key has this digit
         }
     __syncthreads();
-    if (!live || threadIdx.x != 0)
+    if (!a.live || threadIdx.x != 0)
         return;
     if (!one_digit)
-        atomicOr(live, 1u << blockIdx.x);
+        atomicOr(a.live, 1u << blockIdx.x);
     // The last workgroup to finish writes every pass's route code into the
     // upper half of its ticket counter, so that a pass learns its route from
     // the ticket it takes anyway.
     __threadfence();
-    if (atomicAdd(done, 1u) != gridDim.x - 1)
+    if (atomicAdd(a.done, 1u) != gridDim.x - 1)
         return;
     __threadfence();
-    const uint32_t mask = __hip_atomic_load(live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t m = (uint32_t)__builtin_popcount(mask);
-    for (uint32_t q = 0; q < gridDim.x; ++q) {
-        const uint32_t j = (uint32_t)__builtin_popcount(mask & ((1u << q) - 1u));
-        tickets[q] = (unsigned long long)route_code((mask >> q) & 1u, j, m) << 32;
-    }
+    write_plan(__hip_atomic_load(a.live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), gridDim.x, a);
 }
 
 // ------------------------------------------------------------------------
