@@ -128,6 +128,15 @@ __device__ __forceinline__ uint32_t materialize(uint32_t x)
     return x;
 }
 
+// A word that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint64_t uniform(uint64_t x)
+{
+    // each half through uint32_t: the builtin returns a signed int
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Makes a uniform value (a kernel argument) present in scalar registers at
 // this point: its load is issued early instead of at its first use.
 template <typename T>

@@ -1086,8 +1086,7 @@ __global__ __launch_bounds__(THREADS) void seg_radix_pass_kernel(SegPassArgs sa,
     const uint32_t t = __builtin_amdgcn_readfirstlane((uint32_t)L.ticket);
     const uint32_t slot = __builtin_amdgcn_readfirstlane(sa.tile_slot[t]);
     SegLarge g = sa.large[slot];
-    g.begin = (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)g.begin >> 32)) << 32) |
-                        (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)g.begin));
+    g.begin = (int64_t)uniform((uint64_t)g.begin);
     g.len = __builtin_amdgcn_readfirstlane(g.len);
     g.first_tile = __builtin_amdgcn_readfirstlane(g.first_tile);
     RadixPassArgs a = sa.base;

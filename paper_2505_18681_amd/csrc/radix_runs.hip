@@ -68,14 +68,6 @@ __device__ __forceinline__ int bit_above(const uint64_t* set, int at, int words)
         x = set[++w];
     return x ? w * 64 + __ffsll((unsigned long long)x) - 1 : at + 1 + kRunMost;
 }
-// A word that is the same in every lane, in scalar registers.
-__device__ __forceinline__ uint64_t uniform(uint64_t x)
-{
-    // each half through uint32_t: the builtin returns a signed int
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-    return ((uint64_t)hi << 32) | lo;
-}
 // Whether any of the bits lo .. hi is set.
 __device__ __forceinline__ bool any_bit(const uint64_t* set, int lo, int hi)
 {

@@ -271,3 +271,28 @@ def test_segmented_graph_replays_with_new_offsets():
         # eager library work between replays
         x = to_dev(workloads.uniform(np.int32, 50_000, r))
         assert oracle.first_unsorted(to_np(es.sort(x))) == -1
+
+
+def test_segments_past_two_to_the_31():
+    """Segments that begin beyond key 2^31 (their 64-bit position is kept in two 32-bit scalar registers)."""
+    import torch
+
+    es = require_gpu()
+    lead = (1 << 31) + 11
+    sizes = np.array([30_000, 700, 45_001], dtype=np.int64)
+    offs = workloads.segment_offsets(sizes) + lead
+    n = int(offs[-1]) + 3
+    keys = torch.empty(n, dtype=torch.int32, device="cuda")
+    tail = workloads.uniform(np.int32, n - lead, 9)
+    keys[lead:] = to_dev(tail)
+    vals = torch.arange(n - lead, dtype=torch.int32, device="cuda")
+    out = es.segmented_sort(keys, to_dev(offs), out=torch.zeros_like(keys), check=True)
+    assert int(torch.count_nonzero(out[lead - 64:lead])) == 0  # untouched
+    want = oracle.segmented_sort(tail, offs - lead)
+    assert_bits_equal(to_np(out[lead:n - 3]), want[:n - lead - 3], "keys")
+    values = torch.zeros(n, dtype=torch.int32, device="cuda")
+    values[lead:] = vals
+    ko, vo = es.segmented_sort_pairs(keys, values, to_dev(offs), check=True)
+    wk, wv = oracle.segmented_sort_pairs(tail, np.arange(n - lead, dtype=np.int32), offs - lead)
+    assert_bits_equal(to_np(ko[lead:n - 3]), wk[:n - lead - 3], "pairs keys")
+    assert_bits_equal(to_np(vo[lead:n - 3]), wv[:n - lead - 3], "pairs values")
