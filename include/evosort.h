@@ -175,7 +175,9 @@ typedef struct evosort_plan_info {
     uint64_t tile_keys;       /* keys per radix tile, or per mergesort block */
     uint64_t tiles;           /* radix tiles per pass, or mergesort blocks */
     uint32_t merge_rounds;    /* global merge rounds after the block sort (path == MERGE) */
-    uint32_t reserved;
+    uint32_t reserved;        /* with the automatic choice, the sorted blocks of a splitter sort,
+                                 which then runs instead of the routine of `path` (same result)
+                                 where the scratch is at least evosort_temp_bytes; else 0 */
     uint64_t merge_block_run; /* sorted run length after the mergesort block sort */
     uint64_t small_capacity;  /* largest n the one-workgroup sort takes for this dtype/op */
     uint64_t temp_bytes;      /* same as evosort_temp_bytes */

@@ -48,6 +48,7 @@ UNITS = [
     ("capi.cpp", "capi.o", ["-x", "hip"]),
     ("server.cpp", "server.o", ["-x", "hip"]),
     ("noalloc.cpp", "noalloc.o", ["-x", "hip"]),
+    ("split_host.cpp", "split_host.o", ["-x", "hip"]),
 ] + [
     ("radix_inst.hip", f"radix_k{kb}_v{vb}.o", [f"-DEVOSORT_KB={kb}", f"-DEVOSORT_VB={vb}"])
     for kb in (4, 8) for vb in (0, 4, 8)
@@ -57,6 +58,9 @@ UNITS = [
 ] + [
     ("radix_runs.hip", f"radix_runs_k{kb}_v{vb}.o", [f"-DEVOSORT_KB={kb}", f"-DEVOSORT_VB={vb}"])
     for kb in (8,) for vb in (0, 4, 8)
+] + [
+    ("split_sort.hip", f"split_sort_k{kb}_v{vb}.o", [f"-DEVOSORT_KB={kb}", f"-DEVOSORT_VB={vb}"])
+    for kb in (4, 8) for vb in (0, 4, 8)
 ]
 
 
@@ -121,7 +125,8 @@ def _check_no_scratch(usage: dict, what: str):
 
 # Units whose kernels' resource usage is checked at build time.
 CHECKED_UNITS = {"radix_inst.hip": _check_pass_kernels,
-                 "merge.hip": lambda usage: _check_no_scratch(usage, "mergesort")}
+                 "merge.hip": lambda usage: _check_no_scratch(usage, "mergesort"),
+                 "split_sort.hip": lambda usage: _check_no_scratch(usage, "splitter sort")}
 
 
 def _compile(unit, verbose, defines=()):

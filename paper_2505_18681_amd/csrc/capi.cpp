@@ -16,6 +16,7 @@
 #include "radix_shapes.hpp"
 #include "segmented.hpp"
 #include "small_sort.hpp"
+#include "split_sort.hpp"
 #include "tuned_table.hpp"
 
 using namespace evosort;
@@ -143,6 +144,19 @@ constexpr uint32_t kDefaultSpinLimit = 1u << 24;
 constexpr uint32_t kDefaultInsertion = 8;
 constexpr size_t kAlign = 256;
 constexpr int64_t kStatus32Limit = (int64_t)1 << 30;  // 32-bit look-back words hold counts < 2^30
+// Lengths the automatic choice sorts by splitters.  Below, one workgroup is as
+// fast (int32 8000 keys 20.9 us against 20.0, 5000 17.5 against 19.7; int64
+// 2500 28.9 / 22.6; float64 pairs 2048 29.7 / 29.3).  Above, the radix sort is
+// (int32 4e5 keys 55 us against 47, 5e5 58 / 65; argsort of float32 2.6e5
+// 57 / 45, 4e5 61 / 68; int64 3e5 69 us with a prefix sort).  In between, us
+// per sort of the other routines and of this one: int32 16383 36 / 20.5,
+// 1e5 47 / 27; int64 16000 77 / 24, 5e4 67 / 25 (mergesort), 1.3e5 90 / 37;
+// float64 pairs 5e4 91 / 38.
+constexpr int64_t split_least(int key_bytes) { return key_bytes == 4 ? 8193 : 2049; }
+constexpr int64_t split_most(int key_bytes, int val_bytes)
+{
+    return key_bytes == 4 && val_bytes == 0 ? 400000 : (int64_t)1 << 18;
+}
 constexpr int64_t kPrefixMinKeys = (int64_t)1 << 14;  // fewer keys: no prefix sort is considered
 constexpr uint64_t kPrefixMinTiles = 256;  // fewer tiles: pass 0 uses the look-back
 
@@ -278,6 +292,10 @@ struct Plan {
     // merge scratch layout
     MergePlan mp;
     size_t off_mkeys, off_mkeys2, off_mvals, off_parts;
+    // splitter sort scratch layout
+    bool split;  // the automatic choice sorts this length by splitters
+    SplitPlan sp;
+    size_t off_split, off_rows, off_skeys, off_svals, split_total;
     size_t total;
     uint32_t* host_error;  // host-visible error word the kernels also set (null: none)
 };
@@ -484,6 +502,24 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
     } else if (path == EVOSORT_PATH_SMALL) {
         P->off_err = 0;  // the header only: the kernel clears its error word
         off = kAlign;
+    }
+    // The automatic choice with its own parameters: the splitter sort in the
+    // range where it is faster than the routine of the branch.
+    P->split = force == FORCE_NONE && p.algo == EVOSORT_ALGO_AUTO && !p.block_threads && p.digit_bits == 8 &&
+               p.debug_flags == 0 && n >= split_least(kb) && n <= split_most(kb, vb);
+    if (P->split) {
+        P->sp = split_plan(n);
+        P->info.reserved = P->sp.blocks;
+        size_t o = kAlign;
+        P->off_split = o;
+        o = align_up(o + (size_t)P->sp.buckets * 16);
+        P->off_rows = o;
+        o = align_up(o + (size_t)P->sp.blocks * kSplitRow * kb);
+        P->off_skeys = o;
+        o = align_up(o + (size_t)((n + kSplitGroupKeys - 1) / kSplitGroupKeys) * kSplitGroupKeys * kb);
+        P->off_svals = o;
+        o = align_up(o + (size_t)n * vb);
+        P->split_total = o;
     }
     P->total = off;
     P->info.temp_bytes = off;
@@ -743,6 +779,27 @@ evosort_status run_merge(const Plan& P, const void* keys_in, void* keys_out, con
     return EVOSORT_OK;
 }
 
+evosort_status run_split(const Plan& P, const void* keys_in, void* keys_out, const void* vals_in, void* vals_out,
+                         void* temp, hipStream_t s)
+{
+    SplitArgs a{};
+    a.keys_in = keys_in;
+    a.keys_out = P.op == EVOSORT_OP_ARGSORT ? nullptr : keys_out;
+    a.vals_in = vals_in;
+    a.vals_out = vals_out;
+    a.keys_tmp = at(temp, P.off_skeys);
+    a.vals_tmp = P.vb ? at(temp, P.off_svals) : nullptr;
+    a.rows = at(temp, P.off_rows);
+    a.splitters = at(temp, P.off_split);
+    a.n = P.n;
+    a.plan = P.sp;
+    a.iota = P.op == EVOSORT_OP_ARGSORT;
+    a.error_word = reinterpret_cast<uint32_t*>(at(temp, 0));
+    EVOSORT_LAUNCH("split_blocks", s, launch_split_blocks(P.kd, P.vb, a, s));
+    EVOSORT_LAUNCH("split_buckets", s, launch_split_buckets(P.kd, P.vb, a, s));
+    return EVOSORT_OK;
+}
+
 evosort_status sort_impl(int op, int dtype, const void* keys_in, void* keys_out, const void* vals_in, void* vals_out,
                          uint32_t vb, int64_t n, void* temp, size_t temp_bytes, const evosort_params* p,
                          hipStream_t s, uint32_t* host_error)
@@ -768,14 +825,19 @@ evosort_status sort_impl(int op, int dtype, const void* keys_in, void* keys_out,
         return EVOSORT_ERR_TEMP_TOO_SMALL;
     if (P.total > 0 && (!temp || ((uintptr_t)temp & (kAlign - 1))))
         return EVOSORT_ERR_INVALID_ARG;
+    // a scratch that is enough for the routine of the branch only keeps that routine
+    const bool split = P.split && temp_bytes >= P.split_total;
+    const size_t used = split ? P.split_total : P.total;
     // buffers: 0 keys_in, 1 keys_out, 2 vals_in, 3 vals_out, 4 temp
     const void* bufs[5] = {keys_in, op == EVOSORT_OP_ARGSORT ? nullptr : keys_out,
                            op == EVOSORT_OP_SORT_PAIRS ? vals_in : nullptr, op == EVOSORT_OP_SORT ? nullptr : vals_out,
-                           P.total ? temp : nullptr};
-    const size_t sizes[5] = {kbytes, kbytes, vbytes, vbytes, P.total};
+                           used ? temp : nullptr};
+    const size_t sizes[5] = {kbytes, kbytes, vbytes, vbytes, used};
     st = check_buffers(bufs, sizes, 5, 0, 1, 2, 3);
     if (st != EVOSORT_OK)
         return st;
+    if (split)
+        return run_split(P, keys_in, keys_out, vals_in, vals_out, temp, s);
     switch (P.info.path) {
     case EVOSORT_PATH_COPY:
         // n == 1: a temp buffer, if one is given, still gets a clear error word
@@ -1186,7 +1248,7 @@ evosort_status evosort_temp_bytes(int op, int dtype, int64_t n, uint32_t value_b
         return st;
     // Step functions of both routines run on the same scratch.
     Plan R, M;
-    size_t need = P.total;
+    size_t need = P.split && P.split_total > P.total ? P.split_total : P.total;
     if (n > 0 && make_plan(op, dtype, n, value_bytes, p, &R, FORCE_RADIX) == EVOSORT_OK && R.total > need)
         need = R.total;
     if (n > 0 && make_plan(op, dtype, n, value_bytes, p, &M, FORCE_MERGE) == EVOSORT_OK && M.total > need)
