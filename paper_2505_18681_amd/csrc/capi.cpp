@@ -144,15 +144,15 @@ constexpr uint32_t kDefaultSpinLimit = 1u << 24;
 constexpr uint32_t kDefaultInsertion = 8;
 constexpr size_t kAlign = 256;
 constexpr int64_t kStatus32Limit = (int64_t)1 << 30;  // 32-bit look-back words hold counts < 2^30
-// Lengths the automatic choice sorts by splitters.  Below, one workgroup is as
-// fast (int32 8000 keys 20.9 us against 20.0, 5000 17.5 against 19.7; int64
-// 2500 28.9 / 22.6; float64 pairs 2048 29.7 / 29.3).  Above, the radix sort is
-// (int32 4e5 keys 55 us against 47, 5e5 58 / 65; argsort of float32 2.6e5
-// 57 / 45, 4e5 61 / 68; int64 3e5 69 us with a prefix sort).  In between, us
-// per sort of the other routines and of this one: int32 16383 36 / 20.5,
-// 1e5 47 / 27; int64 16000 77 / 24, 5e4 67 / 25 (mergesort), 1.3e5 90 / 37;
+// Lengths the automatic choice sorts by splitters.  Below, one workgroup is
+// faster (int32 8192 keys 14.6 us against 19.4; int64 4096 15 / 23.6) or as
+// fast (argsort of float32 8192 keys 25.9 / 24.5).  Above, the radix sort is
+// (int32 4e5 keys 55 us against 45, 5e5 58 / 65; argsort of float32 2.6e5
+// 57 / 46, 4e5 61 / 68; int64 3e5 69 us with a prefix sort).  In between, us
+// per sort of the other routines and of this one: int32 16383 36 / 19.8,
+// 1e5 47 / 24.5; int64 16000 77 / 24.7, 5e4 67 / 26 (mergesort), 1.3e5 90 / 37;
 // float64 pairs 5e4 91 / 38.
-constexpr int64_t split_least(int key_bytes) { return key_bytes == 4 ? 8193 : 2049; }
+constexpr int64_t split_least(int key_bytes) { return key_bytes == 4 ? 8193 : 4097; }
 constexpr int64_t split_most(int key_bytes, int val_bytes)
 {
     return key_bytes == 4 && val_bytes == 0 ? 400000 : (int64_t)1 << 18;
@@ -1107,7 +1107,6 @@ evosort_status run_segmented(const SegPlan& S, const void* keys_in, void* keys_o
         ba.offsets = offsets;
         ba.list = lists + (size_t)c * S.nseg;
         ba.count = &ctr->class_count[c];
-        ba.ticket = &ctr->class_ticket[c];
         EVOSORT_LAUNCH("seg_block_sort", ss,
                        launch_seg_block_sort(S.kd, S.vb, c, ba, (uint32_t)(bound < 0xffffffffLL ? bound : 0xffffffffLL),
                                              ss));

@@ -241,7 +241,11 @@ __global__ __launch_bounds__((block_threads<KB, VB>())) void merge_block_sort_ke
         const int lane = (int)(threadIdx.x & (kWave - 1));
         const int o = (int)(threadIdx.x / kWave) * kWave * PER;
         for (int L = first_lds_run; L < CAP; L *= 2) {
-            wave_lds_merge<PER>(buf[cur], buf[cur ^ 1], (o / (2 * L)) * (2 * L), L, o, lane, less);
+            W y[PER];
+            wave_lds_merge<PER>(buf[cur], y, (o / (2 * L)) * (2 * L), L, o, lane, less);
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                buf[cur ^ 1][pad16(o + q * kWave + lane)] = y[q];
             __syncthreads();
             cur ^= 1;
         }

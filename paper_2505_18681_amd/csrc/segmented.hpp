@@ -16,8 +16,8 @@
 //   seg_histogram     digit histograms of every pass of every large segment
 //                     (one read), zeroes the look-back words of its tiles;
 //   seg_scan          per large segment and pass: digit bases;
-//   seg_block_sort    persistent workgroups take small segments from their
-//                     class list and sort each in LDS by 8-bit LSD passes;
+//   seg_block_sort    waves or workgroups walk their class's list of small
+//                     segments and sort each in registers and LDS;
 //   seg_radix_pass    one single-sweep pass over all tiles of all large
 //                     segments; a segment's first tile starts its own
 //                     look-back chain.
@@ -35,8 +35,8 @@ namespace evosort {
 constexpr int kSegBits = 8;
 constexpr int kSegBins = 1 << kSegBits;
 
-// One-workgroup classes for records of rb = key bytes + value bytes:
-// workgroup size and keys per thread; capacities ascend.
+// One-workgroup classes for records of rb = key bytes + value bytes; the
+// capacity of a class is threads * items, ascending.
 struct SegClass {
     int threads;
     int items;
@@ -68,7 +68,6 @@ struct SegLarge {
 struct SegCounters {
     uint32_t class_count[kSegMaxClasses + 1];  // [kSegMaxClasses]: large segments
     uint32_t tile_count;
-    uint32_t class_ticket[kSegMaxClasses];
     uint32_t pass_ticket[8];
 };
 
@@ -118,7 +117,6 @@ struct SegBlockArgs {
     const int64_t* offsets;
     const uint32_t* list;
     const uint32_t* count;
-    uint32_t* ticket;
 };
 
 // Arguments of one segmented radix pass: `base` holds the whole-buffer
@@ -137,10 +135,10 @@ hipError_t launch_seg_classify(const SegClassifyArgs& a, hipStream_t s);
 hipError_t launch_seg_setup(const SegLargeArgs& a, uint32_t tile_keys, uint32_t grid, hipStream_t s);
 hipError_t launch_seg_histogram(const KeyDesc& kd, const SegHistArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_seg_scan(const SegLargeArgs& a, uint32_t grid, hipStream_t s);
-// One launch per class: persistent workgroups, at most max_grid of them and
-// no more than fit on the device at once.
+// One launch per class: persistent workgroups, for at most max_segments
+// segments and no more of them than fit on the device at once.
 hipError_t launch_seg_block_sort(const KeyDesc& kd, int val_bytes, int cls, const SegBlockArgs& a,
-                                 uint32_t max_grid, hipStream_t s);
+                                 uint32_t max_segments, hipStream_t s);
 
 // Segmented radix pass (8-bit digits, 32-bit look-back words).
 bool seg_pass_available(int key_bytes, int val_bytes, RadixShape shape);

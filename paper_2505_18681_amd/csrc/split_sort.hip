@@ -52,36 +52,13 @@ constexpr int kSplitThreads = 256;  // of a bucket's workgroup
 static_assert(kSplitBlocksMost <= kSplitThreads, "one thread per block");
 static_assert(kSplitBucketMost == kSplitThreads * 8 && kSplitGroupKeys == kSplitThreads * 8, "eight records per thread");
 
-// Sorts 64 * PER records of every wave in registers, then merges the waves'
-// runs in LDS; the result is in buf[returned], padded (pad16).  WAVES waves.
-template <int WAVES, int PER, typename W, typename Less>
-__device__ __forceinline__ int sort_records(W (&x)[PER], W* buf0, W* buf1, Less less)
-{
-    const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int o = (int)(threadIdx.x / kWave) * kWave * PER;
-    lane_sort(x, less);
-    wave_merge_levels<PER, PER>(x, lane, less);
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-        buf0[pad16((int)threadIdx.x * PER + q)] = x[q];
-    __syncthreads();
-    int cur = 0;
-#pragma unroll
-    for (int L = kWave * PER; L < WAVES * kWave * PER; L *= 2) {
-        wave_lds_merge<PER>(cur ? buf1 : buf0, cur ? buf0 : buf1, (o / (2 * L)) * (2 * L), L, o, lane, less);
-        __syncthreads();
-        cur ^= 1;
-    }
-    return cur;
-}
-
 // ---------------------------------------------------------------- blocks --
 // The splitters: 256 * PER keys of the input, one from each of as many equal
 // parts of it, in order of (key, block); bucket j begins at the sample of rank
 // j / buckets.
 template <int KB, int PER>
 __device__ __forceinline__ void write_splitters(const SplitArgs& a, const OrderMap<typename KeyWord<KB>::U>& om,
-                                                typename Rec<KB>::W* buf0, typename Rec<KB>::W* buf1)
+                                                typename Rec<KB>::W* buf)
 {
     using U = typename KeyWord<KB>::U;
     using SR = Rec<KB>;
@@ -101,11 +78,14 @@ __device__ __forceinline__ void write_splitters(const SplitArgs& a, const OrderM
 #pragma unroll
     for (int q = 0; q < PER; ++q)
         x[q] = SR::make(om.to_order(k[q]), at[q] / a.plan.block_keys);
-    const int cur = sort_records<kSplitThreads / kWave>(x, buf0, buf1,
-                                                        [](const SW& p, const SW& q) { return SR::less(p, q); });
-    const SW* sorted = cur ? buf1 : buf0;
+    sort_striped<kSplitThreads / kWave, false>(x, buf, 0, [](const SW& p, const SW& q) { return SR::less(p, q); });
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        buf[pad16(striped_rank<kSplitThreads / kWave, PER>(q))] = x[q];
+    __syncthreads();
     for (uint32_t j = threadIdx.x; j < a.plan.buckets; j += kSplitThreads)
-        reinterpret_cast<SW*>(a.splitters)[j] = sorted[pad16((int)(j * (uint32_t)S / a.plan.buckets))];
+        reinterpret_cast<SW*>(a.splitters)[j] = buf[pad16((int)(j * (uint32_t)S / a.plan.buckets))];
 }
 
 // BW: waves per block of 512 * BW keys.
@@ -122,17 +102,16 @@ __global__ __launch_bounds__(kSplitThreads) void split_blocks_kernel(SplitArgs a
     constexpr int PART = kWave * PER * BW / kSplitRow;  // keys per entry of an index row
     constexpr size_t BYTES = sizeof(SW) * padded16(G);  // a sample's record is as large as a block's, or larger
     static_assert(sizeof(SW) >= sizeof(W), "the buffers hold either");
-    __shared__ __attribute__((aligned(16))) unsigned char s_buf[2][BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char s_buf[BYTES];
 
     if (blockIdx.x == 0) {  // the first workgroup: its chain is the longest
         if (threadIdx.x == 0 && a.error_word)
             *a.error_word = 0;
-        SW* b0 = reinterpret_cast<SW*>(s_buf[0]);
-        SW* b1 = reinterpret_cast<SW*>(s_buf[1]);
+        SW* buf = reinterpret_cast<SW*>(s_buf);
         if (a.plan.samples == 1024)
-            write_splitters<KB, 4>(a, om, b0, b1);
+            write_splitters<KB, 4>(a, om, buf);
         else
-            write_splitters<KB, 8>(a, om, b0, b1);
+            write_splitters<KB, 8>(a, om, buf);
         return;
     }
     const int64_t start = (int64_t)(blockIdx.x - 1) * G;
@@ -141,39 +120,34 @@ __global__ __launch_bounds__(kSplitThreads) void split_blocks_kernel(SplitArgs a
     const V* vals_in = reinterpret_cast<const V*>(a.vals_in) + start;
     // A wave loads keys of its own block; what is missing in the last block is
     // filled up with records above all of its own.
-    const int i0 = (int)(threadIdx.x / kWave) * kWave * PER + (int)(threadIdx.x & (kWave - 1));
     U k[PER];
     W x[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int i = i0 + q * kWave;
+        const int i = striped_rank<kSplitThreads / kWave, PER>(q);
         k[q] = keys_in[i < cnt ? i : cnt - 1];
     }
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int i = i0 + q * kWave;
+        const int i = striped_rank<kSplitThreads / kWave, PER>(q);
         x[q] = R::make(i < cnt ? om.to_order(k[q]) : ~(U)0, (uint32_t)i);
     }
-    W* b0 = reinterpret_cast<W*>(s_buf[0]);
-    W* b1 = reinterpret_cast<W*>(s_buf[1]);
-    const int cur = sort_records<BW>(x, b0, b1, [](const W& p, const W& q) { return R::less(p, q); });
-    const W* sorted = cur ? b1 : b0;
+    const int first = (int)(threadIdx.x / kWave) / BW * (kWave * PER * BW);  // this wave's block
+    sort_striped<BW, false>(x, reinterpret_cast<W*>(s_buf), first, [](const W& p, const W& q) { return R::less(p, q); });
     U* keys = reinterpret_cast<U*>(a.keys_tmp) + start;
     V* vals = reinterpret_cast<V*>(a.vals_tmp) + start;
+    U* rows = reinterpret_cast<U*>(a.rows) + start / PART;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int i = q * kSplitThreads + (int)threadIdx.x;
+        const int i = striped_rank<kSplitThreads / kWave, PER>(q);
         if (i < cnt) {
-            const W r = sorted[pad16(i)];
-            keys[i] = R::ord(r);
+            keys[i] = R::ord(x[q]);
             if constexpr (VB != 0)
-                vals[i] = a.iota ? (V)(start + R::pos(r)) : vals_in[R::pos(r)];
+                vals[i] = a.iota ? (V)(start + R::pos(x[q])) : vals_in[R::pos(x[q])];
+            if (i % PART == PART - 1)
+                rows[i / PART] = R::ord(x[q]);
         }
     }
-    // entries past the array's end are never used
-    U* rows = reinterpret_cast<U*>(a.rows) + start / PART;
-    for (int e = threadIdx.x; e < G / PART && e * PART < cnt; e += kSplitThreads)
-        rows[e] = R::ord(sorted[pad16(e * PART + PART - 1)]);
 }
 
 // --------------------------------------------------------------- buckets --
@@ -253,7 +227,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_buckets_kernel(SplitArgs 
     constexpr int MOST = kSplitBucketMost;
     constexpr int B = kWave * PER * BW;
     constexpr int PART = B / kSplitRow;  // keys per entry of an index row
-    __shared__ W s_buf[2][padded16(MOST)];
+    __shared__ W s_buf[padded16(MOST)];
     __shared__ uint32_t s_src[MOST];           // where a gathered key comes from
     __shared__ uint32_t s_off[THREADS];        // first gathered key of every block's piece
     __shared__ uint32_t s_from[THREADS];       // where the piece begins in the scratch
@@ -367,18 +341,15 @@ __global__ __launch_bounds__(kSplitThreads) void split_buckets_kernel(SplitArgs 
                 const int e = q * THREADS + (int)threadIdx.x;
                 x[q] = R::make(e < m ? k[q] : ~(U)0, (uint32_t)e);
             }
-            const int cur =
-                sort_records<WAVES>(x, s_buf[0], s_buf[1], [](const W& p, const W& q) { return R::less(p, q); });
-            const W* sorted = s_buf[cur];
+            sort_striped<WAVES, false>(x, s_buf, 0, [](const W& p, const W& q) { return R::less(p, q); });
 #pragma unroll
             for (int q = 0; q < N; ++q) {
-                const int i = q * THREADS + (int)threadIdx.x;
+                const int i = striped_rank<WAVES, N>(q);
                 if (i < m) {
-                    const W r = sorted[pad16(i)];
                     if (keys_out)
-                        keys_out[base + (uint32_t)i] = om.from_order((U)R::ord(r));
+                        keys_out[base + (uint32_t)i] = om.from_order((U)R::ord(x[q]));
                     if constexpr (VB != 0)
-                        vals_out[base + (uint32_t)i] = vals_tmp[s_src[R::pos(r)]];
+                        vals_out[base + (uint32_t)i] = vals_tmp[s_src[R::pos(x[q])]];
                 }
             }
         };

@@ -200,6 +200,33 @@ __device__ __forceinline__ Rec<8>::W lane_xor(const Rec<8>::W& v, int lane)
     return Rec<8>::W{lane_xor<M>(v.ord, lane), lane_xor32<M>(v.pos, lane), 0u};
 }
 
+// One step of a network across lanes: of this lane's record x and its
+// partner's y the lower lane keeps the smaller and the upper the larger one.
+// Bare 32-bit words: the median of both and 0 (the smaller) or all ones (the
+// larger), one instruction where the compare and the select are two.
+template <typename W>
+struct LaneSide {
+    bool high;
+    __device__ __forceinline__ explicit LaneSide(bool h) : high(h) {}
+    template <typename Less>
+    __device__ __forceinline__ W keep(const W& x, const W& y, Less less) const
+    {
+        return pick(less(y, x) != high, y, x);
+    }
+};
+template <>
+struct LaneSide<uint32_t> {
+    uint32_t bound;
+    __device__ __forceinline__ explicit LaneSide(bool h) : bound(h ? ~0u : 0u) {}
+    template <typename Less>
+    __device__ __forceinline__ uint32_t keep(uint32_t x, uint32_t y, Less) const
+    {
+        uint32_t r;
+        asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(bound));
+        return r;
+    }
+};
+
 // Half-cleaner steps of a bitonic merge across lanes: every register of lane
 // l meets the same register of lane l ^ M, for M = M0, M0 / 2, ..., 1; the
 // lower lane keeps the smaller.
@@ -208,12 +235,10 @@ __device__ __forceinline__ void half_clean_lanes(W (&x)[N], int lane, Less less)
 {
     if constexpr (M >= 1) {
         // the lower lane takes y when it is smaller, the upper when it is not
-        const bool high = (lane & M) != 0;
+        const LaneSide<W> side((lane & M) != 0);
 #pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const W y = lane_xor<M>(x[q], lane);
-            x[q] = pick(less(y, x[q]) != high, y, x[q]);
-        }
+        for (int q = 0; q < N; ++q)
+            x[q] = side.keep(x[q], lane_xor<M>(x[q], lane), less);
         half_clean_lanes<M / 2>(x, lane, less);
     }
 }
@@ -231,14 +256,14 @@ __device__ __forceinline__ void wave_merge_levels(W (&x)[PER], int lane, Less le
 {
     if constexpr (L < 64 * PER) {
         constexpr int G = 2 * L / PER;  // lanes holding one pair of runs
-        const bool high = (lane & (G / 2)) != 0;
+        const LaneSide<W> side((lane & (G / 2)) != 0);
         W y[PER];
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             y[q] = lane_xor<G - 1>(x[PER - 1 - q], lane);
 #pragma unroll
         for (int q = 0; q < PER; ++q)
-            x[q] = pick(less(y[q], x[q]) != high, y[q], x[q]);
+            x[q] = side.keep(x[q], y[q], less);
         half_clean_lanes<L / 2 / PER>(x, lane, less);  // distances L/2 .. PER: across lanes
 #pragma unroll
         for (int st = PER / 2; st >= 1; st >>= 1) {
@@ -280,10 +305,11 @@ __device__ __forceinline__ int wave_merge_path(const W* src, int a0, int b0, int
 // on both runs (wave_merge_path), loads its A slice ascending followed by its
 // B slice descending -- a bitonic sequence -- lane-striped (element e in
 // register e / 64 of lane e % 64, so consecutive lanes read consecutive LDS
-// words), sorts it with the half-cleaners of a bitonic merge (distances of 64
-// and more inside the lane, below 64 across lanes) and stores it striped.
+// words), and sorts it with the half-cleaners of a bitonic merge (distances of
+// 64 and more inside the lane, below 64 across lanes): output o + 64 q + lane
+// is left in x[q].
 template <int PER, typename W, typename Less>
-__device__ __forceinline__ void wave_lds_merge(const W* src, W* dst, int s, int L, int o, int lane, Less less)
+__device__ __forceinline__ void wave_lds_merge(const W* src, W (&x)[PER], int s, int L, int o, int lane, Less less)
 {
     constexpr int OUT = 64 * PER;
     const int a0 = s, b0 = s + L;
@@ -292,7 +318,6 @@ __device__ __forceinline__ void wave_lds_merge(const W* src, W* dst, int s, int 
     const int i1 = wave_merge_path(src, a0, b0, L, k + OUT, lane, less);
     const int na = i1 - i0;
     const int b_last = b0 + (k + OUT - i1) - 1;  // the B slice's last element
-    W x[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int e = q * 64 + lane;
@@ -306,9 +331,151 @@ __device__ __forceinline__ void wave_lds_merge(const W* src, W* dst, int s, int 
                 order2(x[q], x[q + d], less);
     }
     half_clean_lanes<32>(x, lane, less);
+}
+
+// Orders the LDS accesses of a wave before and after it (a wave's LDS
+// instructions run in program order; this keeps the compiler to that order).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Sorts the 64 * WAVES * PER records of a group of WAVES consecutive waves,
+// any record of the group in any register, through buf[pad16(first)] .. of
+// padded LDS records: 64 * PER per wave in registers, then merge levels in
+// LDS.  The record of rank r of the group is left in x[q] of the lane with
+// r = (wave of the group) * 64 * PER + 64 q + lane.  With WAVES > 1 every
+// thread of the workgroup has to call it; the buffer may be used again after a
+// barrier (WAVES == 1: after wave_lds_order).
+// LOOPED: called in a loop of the caller, where unrolled merge levels and LDS
+// addresses kept from one round to the next would cost twice the registers.
+template <int WAVES, bool LOOPED, int PER, typename W, typename Less>
+__device__ __forceinline__ void sort_striped(W (&x)[PER], W* buf, int first, Less less)
+{
+    const int tid = (int)(LOOPED ? materialize(threadIdx.x) : threadIdx.x);
+    const int lane = tid & (kWave - 1);
+    const int o = first + (tid / kWave) % WAVES * kWave * PER;  // the wave's first record
+    lane_sort(x, less);
+    wave_merge_levels<PER, PER>(x, lane, less);
+    if constexpr (PER == 1 && WAVES == 1)
+        return;
 #pragma unroll
     for (int q = 0; q < PER; ++q)
-        dst[pad16(o + q * 64 + lane)] = x[q];
+        buf[pad16(o + lane * PER + q)] = x[q];
+    if constexpr (WAVES == 1) {
+        wave_lds_order();
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            x[q] = buf[pad16(o + q * kWave + lane)];
+    } else {
+        __syncthreads();
+        auto level = [&](int L) {
+            wave_lds_merge<PER>(buf, x, first + (o - first) / (2 * L) * (2 * L), L, o, lane, less);
+            if (2 * L < WAVES * kWave * PER) {
+                __syncthreads();  // every wave has read its records
+#pragma unroll
+                for (int q = 0; q < PER; ++q)
+                    buf[pad16(o + q * kWave + lane)] = x[q];
+                __syncthreads();
+            }
+        };
+        if constexpr (LOOPED) {
+#pragma unroll 1
+            for (int L = kWave * PER; L < WAVES * kWave * PER; L *= 2)
+                level(L);
+        } else {
+#pragma unroll
+            for (int L = kWave * PER; L < WAVES * kWave * PER; L *= 2)
+                level(L);
+        }
+    }
+}
+
+// Rank, in its group, of the record that sort_striped leaves in x[q] of this
+// thread.
+template <int WAVES, int PER>
+__device__ __forceinline__ int striped_rank(int q, int tid)
+{
+    return (tid / kWave % WAVES * PER + q) * kWave + (tid & (kWave - 1));
+}
+template <int WAVES, int PER>
+__device__ __forceinline__ int striped_rank(int q)
+{
+    return striped_rank<WAVES, PER>(q, (int)threadIdx.x);
+}
+
+// Where one sort reads and writes.  Values are read from vals_in, or are the
+// input positions when iota is set (argsort); keys are not written when
+// skip_keys is set.
+struct NetworkIo {
+    const void* keys_in;
+    void* keys_out;
+    const void* vals_in;
+    void* vals_out;
+    bool iota;
+    bool skip_keys;
+};
+
+// Sorts keys [begin, begin + len) (1 <= len <= 64 * WAVES * PER), stably, into
+// the same range of the outputs; the outputs may be the inputs.  One group of
+// WAVES waves, as sort_striped.
+template <int KB, int VB, int WAVES, int PER, bool LOOPED>
+__device__ __forceinline__ void network_sort(const NetworkIo& io, const OrderMap<typename KeyWord<KB>::U>& om,
+                                             typename BlockRec<KB, VB>::W* buf, int first, int64_t begin, int len)
+{
+    using U = typename KeyWord<KB>::U;
+    using V = typename ValWord<VB>::T;
+    using R = BlockRec<KB, VB>;
+    using W = typename R::W;
+    const int tid = (int)(LOOPED ? materialize(threadIdx.x) : threadIdx.x);
+    const U* keys_in = reinterpret_cast<const U*>(io.keys_in) + begin;
+    W x[PER];
+    {
+        U k[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = striped_rank<WAVES, PER>(q, tid);
+            k[q] = keys_in[i < len ? i : len - 1];
+        }
+        // filled up with records above all others
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = striped_rank<WAVES, PER>(q, tid);
+            x[q] = R::make(i < len ? om.to_order(k[q]) : ~(U)0, (uint32_t)i);
+        }
+    }
+    sort_striped<WAVES, LOOPED>(x, buf, first, [](const W& p, const W& q) { return R::less(p, q); });
+    if constexpr (VB != 0) {
+        const V* vals_in = reinterpret_cast<const V*>(io.vals_in) + begin;
+        V* vals_out = reinterpret_cast<V*>(io.vals_out) + begin;
+        V v[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = striped_rank<WAVES, PER>(q, tid);
+            const uint32_t at = i < len ? R::pos(x[q]) : 0;
+            v[q] = io.iota ? (V)(begin + at) : vals_in[at];
+        }
+        // in place: every value is read before one is written
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (WAVES > 1)
+            __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = striped_rank<WAVES, PER>(q, tid);
+            if (i < len)
+                vals_out[i] = v[q];
+        }
+    }
+    if (!io.skip_keys) {
+        U* keys_out = reinterpret_cast<U*>(io.keys_out) + begin;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = striped_rank<WAVES, PER>(q, tid);
+            if (i < len)
+                keys_out[i] = om.from_order((U)R::ord(x[q]));
+        }
+    }
 }
 
 }  // namespace evosort

@@ -10,7 +10,7 @@ from gpu_util import assert_bits_equal, require_gpu, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
-RANGE = {4: (8_193, 400_000), 8: (2_049, 262_144)}  # lengths of the route for keys only, by key bytes
+RANGE = {4: (8_193, 400_000), 8: (4_097, 262_144)}  # lengths of the route for keys only, by key bytes
 DTYPES = [np.int32, np.uint32, np.float32, np.int64, np.float64]
 
 
@@ -49,7 +49,7 @@ def _check(es, keys, desc=0, expect=True):
     assert_bits_equal(to_np(k), want, "in place")
 
 
-@pytest.mark.parametrize("n", [2_048, 2_049, 8_192, 8_193, 16_383, 16_385, 100_003, 131_072, 131_073, 262_144, 262_145,
+@pytest.mark.parametrize("n", [4_096, 4_097, 8_192, 8_193, 16_383, 16_385, 100_003, 131_072, 131_073, 262_144, 262_145,
                                400_000, 400_001])
 @pytest.mark.parametrize("dt", [np.int32, np.float64])
 def test_edges_of_the_range(dt, n):
