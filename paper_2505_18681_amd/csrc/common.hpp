@@ -127,6 +127,11 @@ __device__ __forceinline__ uint32_t materialize(uint32_t x)
     asm volatile("" : "+v"(x));
     return x;
 }
+__device__ __forceinline__ uint64_t materialize(uint64_t x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // A word that is the same in every lane, in scalar registers.
 __device__ __forceinline__ uint64_t uniform(uint64_t x)

@@ -595,6 +595,9 @@ struct Status<uint64_t> {
 constexpr uint32_t kFlagAggregate = 1;  // count of this tile only
 constexpr uint32_t kFlagInclusive = 2;  // count of this tile and every tile before it
 
+// Lanes that share one word of counts and lane bits in the rank of 8-bit digits.
+constexpr int kRankLanes = 16;
+
 // Number of predecessor look-back words read at once.  Each agent-scope read
 // crosses to memory (the XCDs' L2s are not coherent with each other), so the
 // walk reads several predecessors per round trip.
@@ -671,6 +674,10 @@ __device__ __forceinline__ uint64_t look_back(const ST* status, uint32_t tile, i
 // items in order i = 0, 1, ... and lanes in order inside an item therefore
 // visits the tile's keys in input order, which is what makes the rank stable.
 
+// With 8-bit digits the unit is a group of 16 lanes (kRankLanes) instead of a
+// wave: group g owns keys [g*16*ITEMS, (g+1)*16*ITEMS), its item i the 16 keys
+// from g*16*ITEMS + i*16 on.
+
 // LDS of one pass workgroup.  The per-wave digit counters and the output
 // staging area are never live at the same time, so they share storage.
 template <int KB, int VB, int BITS, int THREADS, int ITEMS>
@@ -680,13 +687,19 @@ struct PassLds {
     static constexpr int TILE = THREADS * ITEMS;
     // counters [WAVES][BINS] uint32, then (digits up to 11 bits) lane
     // buckets [WAVES][BINS] uint64
-    static constexpr bool kBuckets = BITS <= 11;
+    static constexpr bool kBuckets = BITS <= 11 && BITS != 8;
     static constexpr size_t BUCKET_OFFSET = ((size_t)WAVES * BINS * 4 + 15) & ~(size_t)15;
-    static constexpr size_t HIST_BYTES = BUCKET_OFFSET + (kBuckets ? (size_t)WAVES * BINS * 8 : 0);
+    // 8-bit digits: one word [THREADS / 16][BINS] per 16 lanes and digit (count
+    // and lane bits), and the digit counts of every 256 threads' 16 groups
+    static constexpr bool kGroups = BITS == 8;
+    static constexpr int PARTS = kGroups ? THREADS / BINS : 1;
+    static constexpr size_t HIST_BYTES = kGroups ? (size_t)THREADS / kRankLanes * BINS * 4
+                                                 : BUCKET_OFFSET + (kBuckets ? (size_t)WAVES * BINS * 8 : 0);
     static constexpr size_t STAGE_BYTES = (size_t)TILE * KB + (size_t)(VB ? TILE * VB : 0);
     static constexpr size_t UNION_BYTES = HIST_BYTES > STAGE_BYTES ? HIST_BYTES : STAGE_BYTES;
     __attribute__((aligned(16))) unsigned char uni[UNION_BYTES];
     int64_t gofs[BINS];  // output slot of tile position 0, per digit (32-bit values while n < 2^30)
+    uint32_t part[kGroups ? PARTS * BINS : 1];
     uint32_t wtot[WAVES];
     unsigned long long ticket;  // the workgroup's ticket (route code and tile), shared from the lane that took it
 };
@@ -729,12 +742,15 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
     // Offsets inside the tile are 32-bit; only the tile base is 64-bit.
-    const uint32_t off0 = (uint32_t)(w * WAVE_KEYS + lane);
+    constexpr int STRIDE = Lds::kGroups ? kRankLanes : kWave;  // keys from one item of a thread to the next
+    const int group = (int)threadIdx.x / kRankLanes, glane = (int)threadIdx.x % kRankLanes;
+    const uint32_t off0 =
+        Lds::kGroups ? (uint32_t)(group * kRankLanes * ITEMS + glane) : (uint32_t)(w * WAVE_KEYS + lane);
     const U* __restrict__ tile_keys = reinterpret_cast<const U*>(io.keys_in) + tile_start;
-    // item i of this thread is valid iff i * 64 < rem: one register for all
-    // items instead of one offset per item
+    // item i of this thread is valid iff i * STRIDE < rem: one register for
+    // all items instead of one offset per item
     const int32_t rem = FULL ? 0 : (int32_t)materialize(nvalid - off0);
-    auto item_valid = [&](int i) { return FULL || (int32_t)(i * kWave) < rem; };
+    auto item_valid = [&](int i) { return FULL || (int32_t)(i * STRIDE) < rem; };
 
     // ---- load ----------------------------------------------------------
     // Past the end of the last tile the load is clamped to the last key (in
@@ -743,7 +759,7 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
     V v[VB ? ITEMS : 1];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t off = off0 + (uint32_t)(i * kWave);
+        const uint32_t off = off0 + (uint32_t)(i * STRIDE);
         k[i] = load_off32(tile_keys, FULL ? off : min(off, nvalid - 1));
     }
     if constexpr (VB != 0) {
@@ -751,7 +767,7 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
         const bool iota = (io.flags & RADIX_FLAG_IOTA) != 0;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
-            const uint32_t off = off0 + (uint32_t)(i * kWave);
+            const uint32_t off = off0 + (uint32_t)(i * STRIDE);
             if (iota)
                 v[i] = (V)(tile_start + off);
             else
@@ -762,8 +778,15 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
     // Zero the wave counters and buckets while the loads are in flight (the
     // previous tile's write-out finished reading this storage at the barrier
     // that ended it).
-    for (int i = threadIdx.x; i < WAVES * BINS; i += THREADS)
-        s_whist[i] = 0;
+    if constexpr (Lds::kGroups) {
+        uint4* z = reinterpret_cast<uint4*>(L.uni);
+#pragma unroll
+        for (int i = 0; i < (int)(Lds::HIST_BYTES / 16 / THREADS); ++i)
+            z[i * THREADS + (int)threadIdx.x] = make_uint4(0, 0, 0, 0);
+    } else {
+        for (int i = threadIdx.x; i < WAVES * BINS; i += THREADS)
+            s_whist[i] = 0;
+    }
     if constexpr (Lds::kBuckets) {
         uint64_t* s_bkt = reinterpret_cast<uint64_t*>(L.uni + Lds::BUCKET_OFFSET);
         for (int i = threadIdx.x; i < WAVES * BINS; i += THREADS)
@@ -790,7 +813,38 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
         // materialized now: a deferred pack would keep its operands alive
         rk[i >> 1] = (i & 1) ? materialize(rk[i >> 1] | (r << 16)) : materialize(r);
     };
-    if constexpr (Lds::kBuckets) {
+    if constexpr (Lds::kGroups) {
+        // 8-bit digits: the unit is a group of 16 lanes, whose lane bits and
+        // running count of a digit share one 32-bit word: three LDS accesses
+        // per key (set the bit, read, write the new count) of 4 bytes each,
+        // where a wave's 64-bit bucket and its count take five, two of them of
+        // 8 bytes.  The rank is bound by the LDS pipe (with the buckets 7 of a
+        // tile's 18 us in a pass over 4e8 int32 keys); int32 sorts, buckets /
+        // groups: 5e6 keys 122 / 113 us, 1e7 206 / 190, 3e7 414 / 380, 1e8
+        // 1.112 / 1.075 ms, from 4e8 on equal (memory-bound).
+        uint32_t* gh = s_whist + group * BINS;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t d = (uint32_t)((om.to_order(k[i]) >> a.shift) & (U)(BINS - 1));
+            const bool valid = item_valid(i);
+            // lane 0's digit from one ballot, as below
+            const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
+            const uint64_t same = ballot(d == d0);
+            const uint64_t vmask = FULL ? ~0ull : ballot(valid);
+            if (same != ~0ull && d != d0 && (FULL || valid))
+                atomicOr(&gh[d], 1u << glane);
+            const uint32_t word = gh[d];
+            const uint32_t peers =
+                (d == d0 ? (lane & 32 ? (uint32_t)((same & vmask) >> 32) : (uint32_t)(same & vmask)) >> (lane & 16)
+                         : word) &
+                0xffffu;
+            const uint32_t old = word >> 16;
+            const uint32_t below = (uint32_t)__builtin_popcount(peers & ((1u << glane) - 1u));
+            if ((FULL || valid) && below == 0)
+                gh[d] = (old + (uint32_t)__builtin_popcount(peers)) << 16;
+            put_rank(i, old + below);
+        }
+    } else if constexpr (Lds::kBuckets) {
         uint64_t* bkt = reinterpret_cast<uint64_t*>(L.uni + Lds::BUCKET_OFFSET) + w * BINS;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -849,8 +903,34 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
     // ---- tile counts, publication, in-tile scan ----------------------------
     uint32_t cnt[BPT];
     uint32_t tsum = 0;
+    // 8-bit digits: every thread sums one digit over 16 of the groups (two
+    // counts per register), then 256 threads sum those
+    constexpr int GROUPS = 16;
+    const int part = Lds::kGroups ? (int)threadIdx.x / BINS : 0;
+    uint32_t* part_hist = s_whist + (Lds::kGroups ? (part * GROUPS * BINS + (int)threadIdx.x % BINS) : 0);
+    uint32_t gc[Lds::kGroups ? GROUPS / 2 : 1];
+    if constexpr (Lds::kGroups) {
+        static_assert(THREADS / kRankLanes == Lds::PARTS * GROUPS, "16 groups per 256 threads");
+        uint32_t sum = 0;
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) {
+        for (int g = 0; g < GROUPS / 2; ++g) {
+            const uint32_t lo = part_hist[2 * g * BINS] >> 16, hi = part_hist[(2 * g + 1) * BINS] & 0xffff0000u;
+            gc[g] = lo | hi;
+            sum += lo + (hi >> 16);
+        }
+        L.part[threadIdx.x] = sum;
+        __syncthreads();
+        uint32_t c = 0;
+        if (threadIdx.x < BINS) {
+#pragma unroll
+            for (int q = 0; q < Lds::PARTS; ++q)
+                c += L.part[q * BINS + (int)threadIdx.x];
+        }
+        cnt[0] = c;
+        tsum = c;
+    }
+#pragma unroll
+    for (int j = 0; j < (Lds::kGroups ? 0 : BPT); ++j) {
         const int b = threadIdx.x * BPT + j;
         uint32_t c = 0;
         if (b < BINS) {
@@ -878,7 +958,28 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
 
     // Turn each wave's digit counts into the wave's first local position.
     uint32_t start[BPT];
-    {
+    if constexpr (Lds::kGroups) {
+        start[0] = first;
+        if (threadIdx.x < BINS) {
+            uint32_t r = first;
+#pragma unroll
+            for (int q = 0; q < Lds::PARTS; ++q) {
+                uint32_t* pc = &L.part[q * BINS + (int)threadIdx.x];
+                const uint32_t c = *pc;
+                *pc = r;
+                r += c;
+            }
+        }
+        __syncthreads();
+        uint32_t r = L.part[threadIdx.x];
+#pragma unroll
+        for (int g = 0; g < GROUPS / 2; ++g) {
+            part_hist[2 * g * BINS] = r;
+            r += gc[g] & 0xffffu;
+            part_hist[(2 * g + 1) * BINS] = r;
+            r += gc[g] >> 16;
+        }
+    } else {
         uint32_t run = first;
 #pragma unroll
         for (int j = 0; j < BPT; ++j) {
@@ -903,6 +1004,12 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
     // Done before the look-back so that predecessors get more time to publish.
     // Positions in the tile are below 2^16 and replace the ranks in place,
     // two per word; 0xffff marks an item past the end of the last tile.
+    // The keys are opaque from here on: the order words, digits and LDS
+    // addresses of the rank would otherwise be kept, a register per item.
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        k[i] = materialize(k[i]);
+    const uint32_t own = (uint32_t)(Lds::kGroups ? group : w) * BINS;
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j) {
         uint32_t packed = 0;
@@ -912,7 +1019,7 @@ __device__ __forceinline__ void pass_tile(const RadixPassArgs& a, const PassIo& 
             if (i < ITEMS) {
                 const uint32_t d = (uint32_t)((om.to_order(k[i]) >> a.shift) & (U)(BINS - 1));
                 const uint32_t pos =
-                    item_valid(i) ? s_whist[w * BINS + d] + ((rk[j] >> (16 * h)) & 0xffffu) : 0xffffu;
+                    item_valid(i) ? s_whist[own + d] + ((rk[j] >> (16 * h)) & 0xffffu) : 0xffffu;
                 packed |= pos << (16 * h);
             }
         }

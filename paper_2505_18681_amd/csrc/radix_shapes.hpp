@@ -18,9 +18,12 @@ constexpr size_t radix_lds_bytes(int kb, int vb, int bits, int threads, int item
 {
     const size_t bins = (size_t)1 << bits;
     const size_t counters = (((size_t)(threads / 64) * bins * 4) + 15) & ~(size_t)15;
-    const size_t hist = counters + (bits <= 11 ? (size_t)(threads / 64) * bins * 8 : 0);
+    const size_t buckets = counters + (bits <= 11 ? (size_t)(threads / 64) * bins * 8 : 0);
+    // 8-bit digits: one word per 16 lanes and digit, and one per thread
+    const size_t hist = bits == 8 ? (size_t)(threads / 16) * bins * 4 : buckets;
     const size_t stage = (size_t)threads * items * (size_t)(kb + vb);
-    return (hist > stage ? hist : stage) + bins * 8 + (size_t)(threads / 64) * 4 + 16;
+    return (hist > stage ? hist : stage) + bins * 8 + (size_t)(threads / 64) * 4 + 16 +
+           (bits == 8 ? (size_t)threads * 4 : 4);
 }
 
 // Waves per SIMD the pass kernel must keep so that registers do not cost it
