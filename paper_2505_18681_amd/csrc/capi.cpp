@@ -158,7 +158,6 @@ constexpr int64_t split_most(int key_bytes, int val_bytes)
     return key_bytes == 4 && val_bytes == 0 ? 400000 : (int64_t)1 << 18;
 }
 constexpr int64_t kPrefixMinKeys = (int64_t)1 << 14;  // fewer keys: no prefix sort is considered
-constexpr uint64_t kPrefixMinTiles = 256;  // fewer tiles: pass 0 uses the look-back
 
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -284,8 +283,9 @@ struct Plan {
     uint32_t t_ins;
     // radix scratch layout (byte offsets into temp)
     size_t off_keys_a, off_keys_b, off_vals, off_hist, off_bases, off_status, off_ctr, off_err, off_blocks, off_live,
-        off_done, off_plan, off_sample, off_long;
+        off_done, off_plan, off_long;
     bool prefix_sort;  // a prefix sort may be chosen (SampleArgs, PrefixChoice)
+    uint32_t hist_rows;  // counting workgroups whose counts stay in rows (0: added into zeroed memory)
     bool prefix0;  // pass 0 takes its tile offsets from the histogram's per-tile counts
     size_t zero_begin, zero_end;
     size_t status_pass_bytes;
@@ -444,7 +444,6 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
         P->off_done = 20;  // scan workgroups finished
         P->off_plan = 24;  // the scan's plan word
         P->off_ctr = 64;   // 64-bit ticket counters: passes * 8 <= 128 bytes
-        P->off_sample = 192;  // sample counts (kSampleWords words)
         P->off_long = 232;    // long runs listed
         off = kAlign;
         P->off_hist = off;
@@ -455,21 +454,29 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
         P->zero_end = off;
         P->off_bases = off;
         off = align_up(off + (size_t)passes * bins * 8);
-        // 8-bit digits, all passes in one histogram launch: pass 0's tile
-        // offsets come from per-tile counts and an exclusive scan over tiles
-        // Pass 0 takes its tile offsets from a scan over the histogram's
-        // per-tile counts, which costs three more launches; with few tiles
-        // the look-back is cheaper (int32, ms per sort with / without:
-        // 1e5 0.124 / 0.105, 1e6 0.162 / 0.132, 3e6 (163 tiles) 0.204 /
-        // 0.175, 1e7 (543 tiles) 0.301 / 0.307).
+        // 8-bit digits of 4-byte keys: pass 0 takes its tile offsets from a
+        // scan over the histogram's per-tile counts instead of the look-back.
+        // The scan rides in the launch that makes the digit bases (int32, us
+        // per sort with the look-back / with the scan: 4.2e5 keys 56.0 / 50.1,
+        // 1e6 65.4 / 61.4, 4.5e6 106.7 / 96.8).
         // 8-byte keys: the passes of the lower digits are left out when the
         // upper digits already tell the keys apart (see prefix_choice).
         P->prefix_sort = P->bits == 8 && kb == 8 && n >= kPrefixMinKeys;
-        P->prefix0 = P->bits == 8 && passes == kb && tiles >= kPrefixMinTiles && !P->prefix_sort;
+        P->prefix0 = P->bits == 8 && kb == 4;
         P->off_blocks = off;
-        if (P->prefix0)
+        if (P->prefix0 && tiles > kTilePrefixFused)
             off = align_up(off + (size_t)((tiles + kTilePrefixBlock - 1) / kTilePrefixBlock) * 256 * 8);
         P->off_keys_a = off;
+        P->hist_rows = 0;
+        if (P->bits == 8) {
+            // a few thousand keys at most have no room for them
+            const uint32_t rows = radix_histogram_groups(n, P->prefix0 ? (uint32_t)tiles : 0);
+            const size_t all = (size_t)rows + (rows > kDigitRows ? kRowSums : 0);
+            if (all * passes * bins * 4 <= (size_t)n * kb / 2)  // half is left to the sample
+                P->hist_rows = rows;
+        }
+        if (!P->hist_rows)
+            P->prefix_sort = P->prefix0 = false;
         off = align_up(off + (size_t)n * kb);
         if (op == EVOSORT_OP_ARGSORT) {
             P->off_keys_b = off;
@@ -600,6 +607,7 @@ PrefixChoice prefix_choice(int64_t n, const SampleArgs& sa, bool in_place)
 {
     PrefixChoice c{};
     c.sample = sa.counts;
+    c.groups = sa.groups;
     c.most_pairs = (uint32_t)((int64_t)sa.groups * kSampleKeys * kSampleKeys * kRunMean / (2 * n));
     c.even_stages = in_place;
     return c;
@@ -610,8 +618,8 @@ PrefixChoice prefix_choice(int64_t n, const SampleArgs& sa, bool in_place)
 // launched; on the device each pass learns from the scan which passes have a
 // digit that varies, skips itself if its digit is constant, and otherwise
 // picks its input and output so that the last live pass writes the output
-// (RadixRoute).  A final launch does the copy that an odd number of live
-// passes sorted in place, or no live pass at all, leaves to do.
+// (RadixRoute).  With no live pass the last one copies; sorted in place, a final
+// launch does the copy that an odd number of live passes leaves to do.
 evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, const void* vals_in, void* vals_out,
                          void* temp, hipStream_t s)
 {
@@ -637,26 +645,58 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
     scan.done = done;
     scan.tickets = tickets;
     scan.plan = plan;
-    SampleArgs sample{};
-    if (P.prefix_sort) {
-        sample = prefix_sample(n, reinterpret_cast<uint32_t*>(at(temp, P.off_sample)));
-        scan.prefix = prefix_choice(n, sample, in_place);
-    }
-
-    EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(at(temp, P.zero_begin), P.zero_end - P.zero_begin, s));
-    if (P.prefix0) {
-        void* counts0 = at(temp, P.off_status);  // pass 0's status words hold its tile prefixes
-        EVOSORT_LAUNCH("radix_histogram", s,
-                       launch_radix_histogram_tiles(P.kd, keys_in, n, passes, hist, counts0, (int)P.info.status_bytes,
-                                                    (uint32_t)P.info.tile_keys, (uint32_t)P.info.tiles, s));
-        EVOSORT_LAUNCH("tile_prefix", s,
-                       launch_tile_prefix(counts0, (int)P.info.status_bytes, (uint32_t)P.info.tiles,
-                                          reinterpret_cast<uint64_t*>(at(temp, P.off_blocks)), s));
+    const int status_bytes = (int)P.info.status_bytes;
+    const uint32_t tiles = (uint32_t)P.info.tiles;
+    if (P.hist_rows) {
+        // The histogram's rows (and the sample's) are where the passes' key
+        // buffer is: nothing is written there before the first pass.
+        HistRows out{};
+        out.rows = reinterpret_cast<uint32_t*>(at(temp, P.off_keys_a));
+        uint32_t* sums = out.rows + (size_t)P.hist_rows * passes * bins;
+        uint32_t* sampled = sums + (P.hist_rows > kDigitRows ? (size_t)kRowSums * passes * bins : 0);
+        out.header = at(temp, P.off_err);
+        const size_t zero = P.off_status + (P.prefix0 ? P.status_pass_bytes : 0);
+        out.zero = at(temp, zero);
+        out.zero16 = (P.zero_end - zero) / 16;
+        DigitScanArgs d{};
+        d.rows = out.rows;
+        d.row_count = P.hist_rows;
+        d.passes = (uint32_t)passes;
+        d.n = n;
+        d.tiles = tiles;
+        if (P.prefix0) {
+            void* counts0 = at(temp, P.off_status);  // pass 0's status words hold its tile prefixes
+            EVOSORT_LAUNCH("radix_histogram", s,
+                           launch_radix_histogram_tiles(P.kd, keys_in, n, passes, out, counts0, status_bytes,
+                                                        (uint32_t)P.info.tile_keys, tiles, s));
+            if (tiles <= kTilePrefixFused)
+                d.tile_counts = counts0;
+            else
+                EVOSORT_LAUNCH("tile_prefix", s,
+                               launch_tile_prefix(counts0, status_bytes, tiles,
+                                                  reinterpret_cast<uint64_t*>(at(temp, P.off_blocks)), s));
+        } else {
+            SampleArgs sample{};
+            if (P.prefix_sort) {
+                sample = prefix_sample(n, sampled);
+                scan.prefix = prefix_choice(n, sample, in_place);
+            }
+            EVOSORT_LAUNCH("radix_histogram", s,
+                           launch_radix_histogram(P.kd, keys_in, n, P.bits, passes, hist, out, sample, s));
+        }
+        if (P.hist_rows > kDigitRows) {
+            EVOSORT_LAUNCH("radix_digits", s, launch_radix_rows(out.rows, P.hist_rows, (uint32_t)passes, sums, s));
+            d.rows = sums;
+            d.row_count = kRowSums;
+        }
+        d.scan = scan;
+        EVOSORT_LAUNCH("radix_digits", s, launch_radix_digits(d, status_bytes, s));
     } else {
+        EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(at(temp, P.zero_begin), P.zero_end - P.zero_begin, s));
         EVOSORT_LAUNCH("radix_histogram", s,
-                       launch_radix_histogram(P.kd, keys_in, n, P.bits, passes, hist, sample, s));
+                       launch_radix_histogram(P.kd, keys_in, n, P.bits, passes, hist, HistRows{}, SampleArgs{}, s));
+        EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, P.bits, passes, scan, s));
     }
-    EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, P.bits, passes, scan, s));
 
     RadixRoute r{};
     r.plan = plan;
@@ -686,6 +726,10 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
             a.flags |= RADIX_FLAG_WITHHOLD_T0;
         if (p == 0 && P.prefix0)
             a.flags |= RADIX_FLAG_PREFIX;  // pass 0, when live, is the first live pass: it reads the input
+        // the last pass copies when no pass is live; sorted in place, there may
+        // be a copy after it, which needs a launch of its own
+        if (p + 1 == passes && !in_place && !P.prefix_sort)
+            a.flags |= RADIX_FLAG_COPIES;
         a.spin_limit = P.spin_limit;
         a.tiles = (uint32_t)P.info.tiles;
         a.route = r;
@@ -711,7 +755,8 @@ evosort_status run_radix(const Plan& P, const void* keys_in, void* keys_out, con
         EVOSORT_LAUNCH("radix_long_runs", s, launch_radix_long_runs(P.kd, vb, ra, s));
         return EVOSORT_OK;
     }
-    EVOSORT_LAUNCH("radix_finish", s, launch_radix_finish(r, n, kb, vb, s));
+    if (in_place)
+        EVOSORT_LAUNCH("radix_finish", s, launch_radix_finish(r, n, kb, vb, s));
     return EVOSORT_OK;
 }
 
@@ -1317,7 +1362,8 @@ evosort_status evosort_radix_histogram(int dtype, const void* keys, int64_t n, u
     // hist_out is zeroed and filled directly (row_bytes is a multiple of 16)
     EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(hist_out, row_bytes, s));
     if (n > 0)
-        EVOSORT_LAUNCH("radix_histogram", s, launch_radix_histogram(kd, keys, n, bits, passes, hist_out, SampleArgs{}, s));
+        EVOSORT_LAUNCH("radix_histogram", s, launch_radix_histogram(kd, keys, n, bits, passes, hist_out, HistRows{},
+                                                                     SampleArgs{}, s));
     if (bases_out) {
         ScanArgs sa{};
         sa.bases = bases_out;
@@ -1360,7 +1406,7 @@ evosort_status evosort_radix_pass(int dtype, const void* keys_in, void* keys_out
     auto* bases = reinterpret_cast<uint64_t*>(at(temp, P.off_bases));
     EVOSORT_LAUNCH("fill_zero", s, launch_fill_zero(at(temp, P.zero_begin), P.zero_end - P.zero_begin, s));
     EVOSORT_LAUNCH("radix_histogram", s,
-                   launch_radix_histogram(P.kd, keys_in, n, P.bits, (int)P.info.passes, hist, SampleArgs{}, s));
+                   launch_radix_histogram(P.kd, keys_in, n, P.bits, (int)P.info.passes, hist, HistRows{}, SampleArgs{}, s));
     ScanArgs sa{};
     sa.bases = bases;
     EVOSORT_LAUNCH("radix_scan", s, launch_radix_scan(hist, P.bits, (int)P.info.passes, sa, s));

@@ -78,6 +78,20 @@ __device__ __forceinline__ uint32_t keep_equal_bits(uint32_t acc, uint32_t m, ui
     return __builtin_amdgcn_bitop3_b32(acc, m, sel, 0x90);
 }
 
+// Returns x unchanged, computed at this point: the compiler may not defer the
+// arithmetic that produces x to its first use.  Used where deferring would keep
+// the operands of x (several registers) alive instead of x itself.
+__device__ __forceinline__ uint32_t materialize(uint32_t x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ uint64_t materialize(uint64_t x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Counts one key per active lane into the digit histograms of several
 // passes: hist[p * bins + digit_p(p)] for p = passes - 1 down to 0.  LDS
 // atomics of many lanes on one word are executed one after another, so the
@@ -86,6 +100,9 @@ __device__ __forceinline__ uint32_t keep_equal_bits(uint32_t acc, uint32_t m, ui
 // array); the other lanes add 1 each.  The test stops at the first digit
 // (most significant first) without such a group: random keys pay for one
 // test per key, skewed keys keep the shortcut on every digit that has one.
+// The add's address is opaque: for one that it knows to be the same in every
+// lane the compiler adds a reduction over the wave (3e8 sparse int32 keys: 80 us
+// on the histogram's 650).
 template <class DigitOf>
 __device__ __forceinline__ void lds_count_passes(uint32_t* hist, int bins, int passes, DigitOf&& digit_p)
 {
@@ -100,7 +117,7 @@ __device__ __forceinline__ void lds_count_passes(uint32_t* hist, int bins, int p
             const uint32_t group = (uint32_t)__popcll(same);
             if (group >= 8) {
                 if (lanes_below(act) == 0)
-                    atomicAdd(&hist[p * bins + (int)d0], group);
+                    atomicAdd(&hist[p * bins + (int)materialize(d0)], group);
                 if (d != d0)
                     atomicAdd(&hist[p * bins + (int)d], 1u);
                 continue;
@@ -116,20 +133,6 @@ __device__ __forceinline__ void lds_count_passes(uint32_t* hist, int bins, int p
 __device__ __forceinline__ uint32_t after(uint32_t x, uint32_t y)
 {
     asm volatile("" : "+v"(x) : "v"(y));
-    return x;
-}
-
-// Returns x unchanged, computed at this point: the compiler may not defer the
-// arithmetic that produces x to its first use.  Used where deferring would keep
-// the operands of x (several registers) alive instead of x itself.
-__device__ __forceinline__ uint32_t materialize(uint32_t x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
-}
-__device__ __forceinline__ uint64_t materialize(uint64_t x)
-{
-    asm volatile("" : "+v"(x));
     return x;
 }
 

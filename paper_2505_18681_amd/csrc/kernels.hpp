@@ -27,15 +27,16 @@ struct SampleArgs {
     uint32_t groups = 0;         // sampling workgroups of kSampleKeys keys each (0: none)
     uint32_t heavy_copies = 0;   // copies of one key in a group's sample that make it a heavy key, and
     uint32_t huge_copies = 0;    // a huge one
-    uint32_t* counts = nullptr;  // kSampleWords zeroed words: neighbours by highest differing byte, then SAMPLE_*
+    uint32_t* counts = nullptr;  // kSampleWords words per group: neighbours by highest differing byte, then SAMPLE_*
 };
 constexpr int kSampleKeys = 1024;       // keys per sampling workgroup
 constexpr uint32_t kSampleWords = 10;
 constexpr uint32_t SAMPLE_NEAR = 8;     // 8 - the lowest of the highest bytes in which a heavy key and a neighbour differ
 constexpr uint32_t SAMPLE_HEAVY = 9;    // 1: there is a heavy key, 2: a huge one
-// What a prefix sort is chosen by (radix_scan_kernel).
+// What a prefix sort is chosen by (write_plan).
 struct PrefixChoice {
     const uint32_t* sample = nullptr;  // SampleArgs::counts; null: no prefix sort
+    uint32_t groups = 0;               // SampleArgs::groups
     uint32_t most_pairs = 0;           // sampled neighbours of one prefix that the choice accepts
     bool even_stages = false;          // sorted in place: an odd number of stages would end in the scratch
 };
@@ -48,14 +49,27 @@ struct ScanArgs {
     uint32_t* plan = nullptr;
     PrefixChoice prefix;
 };
+// How a histogram launch of 8-bit digits leaves its counts: added into hist
+// (rows null), or one row of passes * 256 words per counting workgroup, which
+// needs no zeroed memory; the launch then also clears what the later launches
+// need zeroed (the 256-byte header and zero16 16-byte words).
+struct HistRows {
+    uint32_t* rows = nullptr;
+    void* header = nullptr;
+    void* zero = nullptr;
+    size_t zero16 = 0;
+};
+// Counting workgroups (rows) of a launch over n keys; tiles: of
+// launch_radix_histogram_tiles, 0: of launch_radix_histogram.
+uint32_t radix_histogram_groups(int64_t n, uint32_t tiles);
 hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n, int bits, int passes,
-                                  uint64_t* hist, const SampleArgs& sample, hipStream_t s);
+                                  uint64_t* hist, const HistRows& out, const SampleArgs& sample, hipStream_t s);
 
-// The all-pass histogram of 8-bit digits (passes 4 or 8, zeroed hist) that
+// The all-pass histogram of 8-bit digits (passes 4 or 8, counts into rows) that
 // also writes, for every tile of tile_keys keys, the tile's counts of the
 // pass-0 digits: counts[tile * 256 + digit], words of status_bytes (4 or 8).
 hipError_t launch_radix_histogram_tiles(const KeyDesc& kd, const void* keys, int64_t n, int passes,
-                                        uint64_t* hist, void* counts, int status_bytes, uint32_t tile_keys,
+                                        const HistRows& out, void* counts, int status_bytes, uint32_t tile_keys,
                                         uint32_t tiles, hipStream_t s);
 
 // Turns the per-tile counts of launch_radix_histogram_tiles, in place, into
@@ -75,6 +89,29 @@ constexpr uint32_t kTilePrefixBlock = 64;  // tiles per workgroup of the prefix 
 // prefix.sample it may choose a prefix sort from the sample's counts.  Without
 // `live` only the bases are written.
 hipError_t launch_radix_scan(const uint64_t* hist, int bits, int passes, const ScanArgs& a, hipStream_t s);
+
+// The same for counts in rows (HistRows) of 8-bit digits, with everything that
+// launch_radix_scan does with `live`.
+// With tile_counts (tiles <= kTilePrefixFused of them) the launch also does
+// what launch_tile_prefix does.
+struct DigitScanArgs {
+    const uint32_t* rows;
+    uint32_t row_count;
+    uint32_t passes;
+    int64_t n;
+    void* tile_counts;  // null: none
+    uint32_t tiles;
+    ScanArgs scan;
+};
+hipError_t launch_radix_digits(const DigitScanArgs& a, int status_bytes, hipStream_t s);
+// Sums row_count rows of passes * 256 words to kRowSums rows at out.
+hipError_t launch_radix_rows(const uint32_t* rows, uint32_t row_count, uint32_t passes, uint32_t* out, hipStream_t s);
+constexpr uint32_t kDigitRows = 1024;
+constexpr uint32_t kRowSums = 64;
+// Above, three launches (launch_tile_prefix) read the counts with more
+// workgroups (int32, us per sort, three launches / fused: 6e6 keys 126.7 / 116.0,
+// 5e7 (2713 tiles) 547 / 541, 1e8 (5426) 1047 / 1050, 4e8 3813 / 3897).
+constexpr uint32_t kTilePrefixFused = 4096;
 
 // The plan of a routed sort: its number of stages m (live passes, plus one for
 // the run sort of a prefix sort) and the first pass of a prefix sort (0: none).
@@ -110,8 +147,8 @@ __host__ __device__ constexpr uint32_t route_m(uint32_t code) { return (code >> 
 //   argsort:            keys to keys_tmp (j even) or keys_tmp2 (j odd), never
 //                       the last live pass; indices as pairs' values, the
 //                       first live pass taking the input positions.
-// With no live pass the finishing launch copies the input to the output
-// (argsort: writes the identity permutation).
+// With no live pass the last pass, or the finishing launch, copies the input to
+// the output (argsort: writes the identity permutation).
 struct RadixRoute {
     const uint32_t* plan;  // the scan's plan word (read by the run sort and the finishing launch)
     uint32_t pass, passes;
@@ -148,6 +185,8 @@ struct RadixPassArgs {
 constexpr uint32_t RADIX_FLAG_IOTA = 1u;          // values are the input positions (argsort, first pass)
 constexpr uint32_t RADIX_FLAG_SKIP_KEYS = 2u;     // do not write keys (argsort, last pass)
 constexpr uint32_t RADIX_FLAG_WITHHOLD_T0 = 4u;   // debug: tile 0 never publishes
+constexpr uint32_t RADIX_FLAG_COPIES = 16u;       // last pass of a sort with no finishing launch: with no live pass,
+                                                  // the copy to the output (finish_copies)
 constexpr uint32_t RADIX_FLAG_PREFIX = 8u;        // status holds each tile's exclusive digit prefixes, computed
                                                   // before the pass: no publication, no look-back
 

@@ -1,6 +1,5 @@
 // Launchers of the radix histogram and scan kernels, the utility kernels, and
 // the dispatch of the pass kernel over (key bytes, value bytes).
-#include "radix_finish.hpp"
 #include "radix_impl.hpp"
 #include "radix_shapes.hpp"
 
@@ -44,10 +43,9 @@ int histogram_grid(int64_t n)
 {
     // Enough workgroups to fill 256 CUs several times over; each thread then
     // walks the keys with a grid stride.  Up to 2^23 keys at most one per CU:
-    // every workgroup flushes its counts into the same few global words with
-    // atomics, and beyond one workgroup per CU those flushes cost more than
-    // the reads they spread (4-byte keys 2 to 9 % faster from 1.1e6 to 4.6e6
-    // keys; 8-byte keys within 1 %).
+    // beyond that the rows that they leave to sum (or, where they add into
+    // the same few global words, their atomics) cost what the reads they
+    // spread gain (3e6 int64 keys, the whole sort: 156 us with 256 and 512).
     int64_t want = (n + 16 * kHistThreads - 1) / (16 * kHistThreads);
     if (want < 1)
         want = 1;
@@ -62,10 +60,31 @@ int histogram_grid(int64_t n)
         want = 3 * kComputeUnits;
     return (int)want;
 }
+
+// Workgroups of launch_radix_histogram_tiles: each strides over the tiles with
+// 1024 threads, since up to some 1000 tiles one of 256 threads per tile leaves
+// a CU with too few loads in flight (1e7 int32 keys, the whole sort: 256
+// threads 168.4 us, 512 168.0, 1024 165.4; 2e6 keys 79.5, 76.4 and 75.4).  Two
+// per CU fill the chip and are resident at once; large arrays even out the CUs
+// with more (1e8 int32 keys 1033 us with 512 and 1024, 1045 with 2048; 1e9
+// 9.32 ms with 512, 9.26 with 1024).  Each leaves a row of 4 KB to sum.
+constexpr int kTileHistThreads = 1024;
+uint32_t tile_histogram_grid(uint32_t tiles)
+{
+    const uint32_t want = (uint32_t)(tiles < 8192 ? 2 : (tiles < 16384 ? 4 : 16)) * (uint32_t)kComputeUnits;
+    return tiles < want ? tiles : want;
+}
 }  // namespace
 
+uint32_t radix_histogram_groups(int64_t n, uint32_t tiles)
+{
+    if (tiles == 0)
+        return (uint32_t)histogram_grid(n);
+    return tile_histogram_grid(tiles);
+}
+
 hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n, int bits, int passes,
-                                  uint64_t* hist, const SampleArgs& sample, hipStream_t s)
+                                  uint64_t* hist, const HistRows& out, const SampleArgs& sample, hipStream_t s)
 {
     // LDS budget of one launch: 64 KB of 32-bit counters.  Group the passes so
     // that each group has at least one private copy; add copies (at most one
@@ -74,23 +93,22 @@ hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n
     if (bits == 8 && (passes == 4 || passes == 8)) {
         // every pass in one launch, one set of counters per workgroup (as in
         // launch_radix_histogram_tiles)
-        const int grid = histogram_grid(n) + (int)sample.groups;
-        const int copies = 1;
-        size_t lds = (size_t)copies * passes * per_pass;
+        const int grid = (int)radix_histogram_groups(n, 0) + (int)sample.groups;
+        size_t lds = (size_t)passes * per_pass;
         if (sample.groups && lds < (size_t)kSampleKeys * kd.bytes)
             lds = (size_t)kSampleKeys * kd.bytes;
         auto* h = reinterpret_cast<unsigned long long*>(hist);
         if (kd.bytes == 4 && passes == 4) {
             OrderMap<uint32_t> om{(uint32_t)kd.flip, (uint32_t)kd.neg, (uint32_t)kd.desc};
             hipLaunchKernelGGL((radix_histogram8_kernel<4, kHistThreads, 4>), dim3(grid), dim3(kHistThreads), lds,
-                               s, reinterpret_cast<const uint32_t*>(keys), n, om, copies, h,
+                               s, reinterpret_cast<const uint32_t*>(keys), n, om, h, out,
                                sample);
             return hipGetLastError();
         }
         if (kd.bytes == 8 && passes == 8) {
             OrderMap<uint64_t> om{kd.flip, kd.neg, kd.desc};
             hipLaunchKernelGGL((radix_histogram8_kernel<8, kHistThreads, 8>), dim3(grid), dim3(kHistThreads), lds,
-                               s, reinterpret_cast<const uint64_t*>(keys), n, om, copies, h,
+                               s, reinterpret_cast<const uint64_t*>(keys), n, om, h, out,
                                sample);
             return hipGetLastError();
         }
@@ -123,48 +141,29 @@ hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n
 }
 
 hipError_t launch_radix_histogram_tiles(const KeyDesc& kd, const void* keys, int64_t n, int passes,
-                                        uint64_t* hist, void* counts, int status_bytes, uint32_t tile_keys,
+                                        const HistRows& out, void* counts, int status_bytes, uint32_t tile_keys,
                                         uint32_t tiles, hipStream_t s)
 {
     if (tiles == 0)
         return hipSuccess;
-    // One set of counters per workgroup: LDS atomics of different waves on
-    // one counter are separate instructions and do not conflict, and the
-    // smaller footprint lets more workgroups share a CU (one copy per wave:
-    // 1e9 int64 keys 2.32 ms, one per workgroup 2.16 ms; int32 keys equal).
-    const int copies = 1;
-    const size_t lds = ((size_t)copies * passes + 1) * 256 * 4;
-    // Workgroups stride over the tiles, about three tiles each, between 2048
-    // and 16384 workgroups: every workgroup flushes its counts with global
-    // atomics, so fewer of them flush less, while 16384 keep the largest
-    // arrays' reads in flight (int32 keys: 1e9 1.06 ms with 16384 against
-    // 1.10 and 1.07 with 4096 and 8192; 1e8 0.158 ms with 2048 against 0.181
-    // with one workgroup per tile).  The kernel is bound by the throughput
-    // of its LDS atomics: 4 per 4-byte key, one per digit position.
-    const uint32_t third = tiles / 3;
-    const uint32_t want = third < 2048 ? 2048 : (third > 16384 ? 16384 : third);
-    const uint32_t grid = tiles < want ? tiles : want;
-    auto* h = reinterpret_cast<unsigned long long*>(hist);
-#define EVOSORT_HT(KB, P, ST, U)                                                                                 \
-    do {                                                                                                       \
-        OrderMap<U> om{(U)kd.flip, (U)kd.neg, (U)kd.desc};                                                                 \
-        hipLaunchKernelGGL((radix_histogram8_tiles_kernel<KB, kHistThreads, P, ST>), dim3(grid),                \
-                           dim3(kHistThreads), lds, s, reinterpret_cast<const U*>(keys), n, om, copies, h,      \
-                           reinterpret_cast<ST*>(counts), tile_keys, tiles);                                   \
-        return hipGetLastError();                                                                              \
-    } while (0)
-    if (kd.bytes == 4 && passes == 4) {
-        if (status_bytes == 4)
-            EVOSORT_HT(4, 4, uint32_t, uint32_t);
-        EVOSORT_HT(4, 4, uint64_t, uint32_t);
-    }
-    if (kd.bytes == 8 && passes == 8) {
-        if (status_bytes == 4)
-            EVOSORT_HT(8, 8, uint32_t, uint64_t);
-        EVOSORT_HT(8, 8, uint64_t, uint64_t);
-    }
-#undef EVOSORT_HT
-    return hipErrorInvalidValue;
+    if (kd.bytes != 4 || passes != 4)
+        return hipErrorInvalidValue;
+    const OrderMap<uint32_t> om{(uint32_t)kd.flip, (uint32_t)kd.neg, (uint32_t)kd.desc};
+    const auto* k = reinterpret_cast<const uint32_t*>(keys);
+    const uint32_t grid = radix_histogram_groups(n, tiles);
+    // One set of counters per workgroup: LDS atomics of different waves on one
+    // counter are separate instructions and do not conflict.  Their throughput,
+    // 4 per key, is what bounds the kernel.
+    const size_t lds = ((size_t)passes + 1) * 256 * 4;
+    if (status_bytes == 4)
+        hipLaunchKernelGGL((radix_histogram8_tiles_kernel<4, kTileHistThreads, 4, uint32_t>), dim3(grid),
+                           dim3(kTileHistThreads), lds, s, k, n, om, out, reinterpret_cast<uint32_t*>(counts),
+                           tile_keys, tiles);
+    else
+        hipLaunchKernelGGL((radix_histogram8_tiles_kernel<4, kTileHistThreads, 4, uint64_t>), dim3(grid),
+                           dim3(kTileHistThreads), lds, s, k, n, om, out, reinterpret_cast<uint64_t*>(counts),
+                           tile_keys, tiles);
+    return hipGetLastError();
 }
 
 hipError_t launch_tile_prefix(void* counts, int status_bytes, uint32_t tiles, uint64_t* block_sums, hipStream_t s)
@@ -191,6 +190,22 @@ hipError_t launch_tile_prefix(void* counts, int status_bytes, uint32_t tiles, ui
     else
         hipLaunchKernelGGL(tile_prefix_kernel<uint64_t>, dim3(blocks), dim3(256), 0, s,
                            reinterpret_cast<uint64_t*>(counts), tiles, block_sums);
+    return hipGetLastError();
+}
+
+hipError_t launch_radix_rows(const uint32_t* rows, uint32_t row_count, uint32_t passes, uint32_t* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(radix_rows_kernel<256>, dim3(passes, kRowSums), dim3(256), 0, s, rows, row_count, passes * 256, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_radix_digits(const DigitScanArgs& a, int status_bytes, hipStream_t s)
+{
+    const uint32_t grid = a.passes + (a.tile_counts ? 256 / kDigitTile : 0);
+    if (status_bytes == 4)
+        hipLaunchKernelGGL(radix_digits_kernel<uint32_t>, dim3(grid), dim3(kDigitThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(radix_digits_kernel<uint64_t>, dim3(grid), dim3(kDigitThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -5,8 +5,10 @@
 //                           every pass (the paper recounts before each pass;
 //                           the count of a digit position does not depend on
 //                           the order the keys are in, so one read suffices);
-//   radix_scan_kernel       exclusive prefix sums of each pass's histogram:
-//                           the first output slot of every digit;
+//   radix_digits_kernel     exclusive prefix sums of each pass's histogram:
+//                           the first output slot of every digit, and of the
+//                           tiles' counts of pass 0's digits
+//                           (radix_scan_kernel at other digit widths);
 //   radix_pass_kernel       one pass: rank a tile of keys stably by digit
 //                           inside the workgroup, find the tile's offset within
 //                           each digit's output range by a chained scan over
@@ -17,6 +19,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "radix_finish.hpp"
 #include "segmented.hpp"
 
 namespace evosort {
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(THREADS) void radix_histogram_kernel(const typename
 
 // One thread: the routes of a sort's passes and its plan, from the mask of the
 // passes whose digit takes more than one value.
-__device__ __forceinline__ void write_plan(uint32_t mask, uint32_t passes, const ScanArgs& a)
+__device__ __forceinline__ void write_plan(uint32_t mask, uint32_t passes, const ScanArgs& a, const uint32_t* sample)
 {
     // A prefix sort from pass p0 on: the highest p0 whose upper digits leave
     // few sampled neighbours untold apart (runs of about kRunMean keys at
@@ -109,8 +112,7 @@ __device__ __forceinline__ void write_plan(uint32_t mask, uint32_t passes, const
     // some 65536 times less likely than one that the sample would show), and
     // huge runs are left to the passes.
     uint32_t p0 = 0;
-    if (a.prefix.sample) {
-        const uint32_t* sample = a.prefix.sample;
+    if (sample) {
         const uint32_t near = sample[SAMPLE_NEAR], heavy = sample[SAMPLE_HEAVY];
         uint32_t untold = 0;
         for (uint32_t q = 1; q + 1 < passes; ++q) {
@@ -252,12 +254,21 @@ __device__ void sample_keys(const typename KeyWord<KB>::U* __restrict__ keys, in
             atomicMax(&found[SAMPLE_NEAR], 8u - byte);
     }
     __syncthreads();
-    if (threadIdx.x < kSampleWords && found[threadIdx.x]) {
-        if (threadIdx.x < SAMPLE_NEAR)
-            atomicAdd(&sa.counts[threadIdx.x], found[threadIdx.x]);
-        else
-            atomicMax(&sa.counts[threadIdx.x], found[threadIdx.x]);
-    }
+    if (threadIdx.x < kSampleWords)
+        sa.counts[(size_t)group * kSampleWords + threadIdx.x] = found[threadIdx.x];
+}
+
+// What a counting workgroup does first (HistRows): clears its part of the
+// memory that the later launches need zeroed.
+template <int THREADS>
+__device__ __forceinline__ void clear_for_passes(const HistRows& out, uint32_t block, uint32_t blocks)
+{
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    if (block == 0 && threadIdx.x < 16 && out.header)
+        reinterpret_cast<uint4*>(out.header)[threadIdx.x] = z;
+    uint4* p = reinterpret_cast<uint4*>(out.zero);
+    for (size_t i = (size_t)block * THREADS + threadIdx.x; i < out.zero16; i += (size_t)blocks * THREADS)
+        p[i] = z;
 }
 
 // The same for 8-bit digits and all passes in one launch (the common case),
@@ -267,8 +278,8 @@ __device__ void sample_keys(const typename KeyWord<KB>::U* __restrict__ keys, in
 template <int KB, int THREADS, int PASSES>
 __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typename KeyWord<KB>::U* __restrict__ keys,
                                                                    int64_t n, OrderMap<typename KeyWord<KB>::U> om,
-                                                                   int copies, unsigned long long* __restrict__ hist,
-                                                                   SampleArgs sample)
+                                                                   unsigned long long* __restrict__ hist,
+                                                                   HistRows out, SampleArgs sample)
 {
     using U = typename KeyWord<KB>::U;
     constexpr int BINS = 256;
@@ -280,20 +291,21 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typenam
         sample_keys<KB, THREADS>(keys, n, om, blockIdx.x, sample, reinterpret_cast<U*>(lds_hist), found);
         return;
     }
-    for (int i = threadIdx.x; i < copies * PER_COPY; i += THREADS)
+    const uint32_t block = blockIdx.x - sample.groups, blocks = gridDim.x - sample.groups;
+    clear_for_passes<THREADS>(out, block, blocks);
+    for (int i = threadIdx.x; i < PER_COPY; i += THREADS)
         lds_hist[i] = 0;
     __syncthreads();
 
-    uint32_t* mine = lds_hist + (int)((threadIdx.x / kWave) % copies) * PER_COPY;
     auto count = [&](U k) {
         const U u = om.to_order(k);
-        lds_count_passes(mine, BINS, PASSES, [&](int p) { return (uint32_t)(u >> (8 * p)) & 0xffu; });
+        lds_count_passes(lds_hist, BINS, PASSES, [&](int p) { return (uint32_t)(u >> (8 * p)) & 0xffu; });
     };
 
     constexpr int VEC = 16 / KB;
     constexpr int UNROLL = 4;
-    const int64_t stride = (int64_t)(gridDim.x - sample.groups) * THREADS;
-    const int64_t gtid = (int64_t)(blockIdx.x - sample.groups) * THREADS + threadIdx.x;
+    const int64_t stride = (int64_t)blocks * THREADS;
+    const int64_t gtid = (int64_t)block * THREADS + threadIdx.x;
     int64_t done = 0;
     if ((reinterpret_cast<uintptr_t>(keys) & 15) == 0) {
         const int64_t nvec = n / VEC;
@@ -328,10 +340,10 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typenam
     __syncthreads();
 
     for (int i = threadIdx.x; i < PER_COPY; i += THREADS) {
-        uint32_t s = 0;
-        for (int c = 0; c < copies; ++c)
-            s += lds_hist[c * PER_COPY + i];
-        if (s)
+        const uint32_t s = lds_hist[i];
+        if (out.rows)
+            out.rows[(size_t)block * PER_COPY + i] = s;
+        else if (s)
             atomicAdd(&hist[i], (unsigned long long)s);
     }
 }
@@ -345,19 +357,19 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_kernel(const typenam
 // here; those of later passes depend on the previous pass's output.
 template <int KB, int THREADS, int PASSES, typename ST>
 __global__ __launch_bounds__(THREADS) void radix_histogram8_tiles_kernel(
-    const typename KeyWord<KB>::U* __restrict__ keys, int64_t n, OrderMap<typename KeyWord<KB>::U> om, int copies,
-    unsigned long long* __restrict__ hist, ST* __restrict__ counts, uint32_t tile_keys, uint32_t tiles)
+    const typename KeyWord<KB>::U* __restrict__ keys, int64_t n, OrderMap<typename KeyWord<KB>::U> om, HistRows out,
+    ST* __restrict__ counts, uint32_t tile_keys, uint32_t tiles)
 {
     using U = typename KeyWord<KB>::U;
     constexpr int BINS = 256;
     constexpr int PER_COPY = PASSES * BINS;
-    extern __shared__ uint32_t lds_hist[];  // copies * PER_COPY, then the tile's pass-0 row
-    uint32_t* tile_row = lds_hist + copies * PER_COPY;
-    for (int i = threadIdx.x; i < copies * PER_COPY + BINS; i += THREADS)
+    extern __shared__ uint32_t lds_hist[];  // PER_COPY, then the tile's pass-0 row
+    uint32_t* tile_row = lds_hist + PER_COPY;
+    clear_for_passes<THREADS>(out, blockIdx.x, gridDim.x);
+    for (int i = threadIdx.x; i < PER_COPY + BINS; i += THREADS)
         lds_hist[i] = 0;
     __syncthreads();
 
-    uint32_t* mine = lds_hist + (int)((threadIdx.x / kWave) % copies) * PER_COPY;
     // as lds_count_passes, with pass 0 counted into the tile's row
     auto count = [&](U k) {
         const U u = om.to_order(k);
@@ -365,7 +377,7 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_tiles_kernel(
         bool check = true;  // wave-uniform
 #pragma unroll
         for (int p = PASSES - 1; p >= 0; --p) {
-            uint32_t* row = p == 0 ? tile_row : mine + p * BINS;
+            uint32_t* row = p == 0 ? tile_row : lds_hist + p * BINS;
             const uint32_t d = (uint32_t)(u >> (8 * p)) & 0xffu;
             if (check) {
                 const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
@@ -373,7 +385,7 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_tiles_kernel(
                 const uint32_t group = (uint32_t)__popcll(same);
                 if (group >= 8) {
                     if (lanes_below(act) == 0)
-                        atomicAdd(&row[d0], group);
+                        atomicAdd(&row[materialize(d0)], group);
                     if (d != d0)
                         atomicAdd(&row[d], 1u);
                     continue;
@@ -423,7 +435,7 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_tiles_kernel(
         for (int64_t i = done + threadIdx.x; i < len; i += THREADS)
             count(tk[i]);
         __syncthreads();
-        // the tile's pass-0 counts go out and into the pass-0 row of copy 0
+        // the tile's pass-0 counts go out and into the pass-0 row
         for (int b = threadIdx.x; b < BINS; b += THREADS) {
             const uint32_t c = tile_row[b];
             counts[(size_t)t * BINS + b] = (ST)c;
@@ -433,13 +445,8 @@ __global__ __launch_bounds__(THREADS) void radix_histogram8_tiles_kernel(
         __syncthreads();
     }
 
-    for (int i = threadIdx.x; i < PER_COPY; i += THREADS) {
-        uint32_t s = 0;
-        for (int c = 0; c < copies; ++c)
-            s += lds_hist[c * PER_COPY + i];
-        if (s)
-            atomicAdd(&hist[i], (unsigned long long)s);
-    }
+    for (int i = threadIdx.x; i < PER_COPY; i += THREADS)
+        out.rows[(size_t)blockIdx.x * PER_COPY + i] = lds_hist[i];
 }
 
 // Exclusive prefix over tiles of per-tile digit counts (256 digits, one
@@ -574,7 +581,181 @@ __global__ __launch_bounds__(THREADS) void radix_scan_kernel(const uint64_t* __r
     if (atomicAdd(a.done, 1u) != gridDim.x - 1)
         return;
     __threadfence();
-    write_plan(__hip_atomic_load(a.live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), gridDim.x, a);
+    write_plan(__hip_atomic_load(a.live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), gridDim.x, a, nullptr);
+}
+
+// The digit bases, the plan and the tile prefixes in one launch, from the
+// histogram's rows (HistRows).  Workgroup p < passes sums pass p's digits over
+// all rows (64 threads read the 1 KB of a row, 16 rows at a time, 16 in flight
+// per thread) and scans them.  Whether the pass is live goes to the others in
+// the word that counts the finished workgroups, so that no fence is needed, and
+// the last one writes the plan.  The other 16 turn 16 digits of the per-tile
+// counts into prefixes: 64 groups of threads hold a range of tiles each, in
+// registers when the range is short.  It is bound by its chain of memory round
+// trips, not by its bytes: with 8 summing workgroups per pass, whose last one
+// scans all passes, it took 9.0 us instead of 5.4 at 1e6 int32 keys.
+constexpr int kDigitThreads = 1024;
+
+// Many rows (more than kDigitRows) to kRowSums: the few workgroups above take
+// 37 us to read 8 MB of them, this launch's 64 * passes 5 us.  A row's sums
+// stay in 32 bits: each is of 1/64 of the workgroups' keys.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void radix_rows_kernel(const uint32_t* __restrict__ rows, uint32_t row_count,
+                                                        uint32_t words, uint32_t* __restrict__ out)
+{
+    const uint32_t* col = rows + blockIdx.x * 256 + threadIdx.x;
+    uint32_t s = 0;
+    for (uint32_t r = blockIdx.y; r < row_count; r += 8 * kRowSums) {
+        uint32_t c[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+            c[j] = col[(size_t)(r + j * kRowSums < row_count ? r + j * kRowSums : r) * words];  // no branch
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+            s += r + j * kRowSums < row_count ? c[j] : 0;
+    }
+    out[(size_t)blockIdx.y * words + blockIdx.x * 256 + threadIdx.x] = s;
+}
+
+constexpr int kDigitTile = 16;  // digits per tile workgroup
+
+template <typename ST>
+__device__ __forceinline__ void tile_prefix_digits(ST* __restrict__ counts, uint32_t tiles, uint32_t digit0,
+                                                   uint64_t* part)
+{
+    constexpr uint32_t SEGS = kDigitThreads / kDigitTile;
+    static_assert(SEGS == kWave && kDigitTile == kDigitThreads / kWave, "a wave scans the groups of one digit");
+    constexpr uint32_t B = kTilePrefixBatch;
+    const uint32_t d = threadIdx.x % kDigitTile, seg = threadIdx.x / kDigitTile;
+    const uint32_t per = (tiles + SEGS - 1) / SEGS;
+    const uint32_t t0 = seg * per < tiles ? seg * per : tiles, t1 = t0 + per < tiles ? t0 + per : tiles;
+    ST* col = counts + digit0 + d;
+    ST c[B];
+    auto load = [&](uint32_t tb) {
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j)
+            c[j] = col[(size_t)(tb + j < t1 ? tb + j : tiles - 1) * 256];  // no branch
+    };
+    uint64_t s = 0;
+    for (uint32_t tb = t0; tb < t1; tb += B) {
+        load(tb);
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j)
+            s += tb + j < t1 ? (uint64_t)c[j] : 0;
+    }
+    part[seg * (kDigitTile + 1) + d] = s;
+    __syncthreads();
+    {
+        uint64_t* p = part + (threadIdx.x & (kWave - 1)) * (kDigitTile + 1) + threadIdx.x / kWave;
+        const uint64_t mine = *p;
+        uint64_t x = mine;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint64_t y = __shfl_up(x, o, kWave);
+            if ((int)(threadIdx.x & (kWave - 1)) >= o)
+                x += y;
+        }
+        *p = x - mine;
+    }
+    __syncthreads();
+    uint64_t run = part[seg * (kDigitTile + 1) + d];
+    for (uint32_t tb = t0; tb < t1; tb += B) {
+        if (per > B)
+            load(tb);
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j) {
+            if (tb + j < t1) {
+                col[(size_t)(tb + j) * 256] = (ST)run;
+                run += (uint64_t)c[j];
+            }
+        }
+    }
+}
+
+template <typename ST>
+__global__ __launch_bounds__(kDigitThreads) void radix_digits_kernel(DigitScanArgs a)
+{
+    constexpr uint32_t SEGS = kDigitThreads / kWave;
+    __shared__ uint64_t part[SEGS * 256];
+    __shared__ uint64_t wave_sum[4];
+    __shared__ uint32_t sample[kSampleWords];
+    __shared__ uint32_t one_digit;
+    static_assert(SEGS * 256 >= kWave * (kDigitTile + 1), "the tile workgroups' part");
+    if (blockIdx.x >= a.passes) {
+        tile_prefix_digits(reinterpret_cast<ST*>(a.tile_counts), a.tiles, (blockIdx.x - a.passes) * kDigitTile, part);
+        return;
+    }
+    if (threadIdx.x < kSampleWords)
+        sample[threadIdx.x] = 0;
+    if (threadIdx.x == 0)
+        one_digit = 0;
+    const uint32_t lane = threadIdx.x & (kWave - 1), seg = threadIdx.x / kWave;
+    const size_t row_quads = (size_t)a.passes * 64;
+    const uint4* col = reinterpret_cast<const uint4*>(a.rows) + (size_t)blockIdx.x * 64 + lane;
+    uint64_t s[4] = {};
+    constexpr uint32_t B = 16;
+    for (uint32_t r = seg; r < a.row_count; r += B * SEGS) {
+        uint4 c[B];
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j)
+            c[j] = col[(size_t)(r + j * SEGS < a.row_count ? r + j * SEGS : r) * row_quads];  // no branch
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j) {
+            const bool in = r + j * SEGS < a.row_count;
+            s[0] += in ? c[j].x : 0;
+            s[1] += in ? c[j].y : 0;
+            s[2] += in ? c[j].z : 0;
+            s[3] += in ? c[j].w : 0;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        part[seg * 256 + lane * 4 + j] = s[j];
+    __syncthreads();
+    uint64_t c = 0, x = 0;
+    if (threadIdx.x < 256) {
+#pragma unroll
+        for (uint32_t j = 0; j < SEGS; ++j)
+            c += part[j * 256 + threadIdx.x];
+        x = c;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint64_t y = __shfl_up(x, o, kWave);
+            if ((int)lane >= o)
+                x += y;
+        }
+        if (lane == kWave - 1)
+            wave_sum[seg] = x;
+        if (c == (uint64_t)a.n)
+            one_digit = 1;  // every key has this digit
+    }
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        for (uint32_t w = 0; w < seg; ++w)
+            x += wave_sum[w];
+        a.scan.bases[(size_t)blockIdx.x * 256 + threadIdx.x] = x - c;
+    } else if (a.scan.prefix.sample && threadIdx.x >= kDigitThreads / 2) {
+        const uint32_t t = threadIdx.x - kDigitThreads / 2, word = t % 16;
+        if (word < kSampleWords) {
+            uint32_t v = 0;
+            for (uint32_t g = t / 16; g < a.scan.prefix.groups; g += kDigitThreads / 32) {
+                const uint32_t f = a.scan.prefix.sample[(size_t)g * kSampleWords + word];
+                v = word < SAMPLE_NEAR ? v + f : (f > v ? f : v);
+            }
+            if (v && word < SAMPLE_NEAR)
+                atomicAdd(&sample[word], v);
+            else if (v)
+                atomicMax(&sample[word], v);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x != 0)
+        return;
+    // workgroups finished in the low byte, live passes above it
+    const uint32_t mine = 1u + (one_digit ? 0u : 256u << blockIdx.x);
+    const uint32_t all = atomicAdd(a.scan.done, mine) + mine;
+    if ((all & 255u) == a.passes)
+        write_plan(all >> 8, a.passes, a.scan, a.scan.prefix.sample ? sample : nullptr);
 }
 
 // ------------------------------------------------------------------------
@@ -1150,8 +1331,13 @@ __global__ __launch_bounds__(THREADS) void radix_pass_kernel(RadixPassArgs a, Or
     const uint32_t tile = __builtin_amdgcn_readfirstlane((uint32_t)t);
     PassIo io{a.keys_in, a.keys_out, a.vals_in, a.vals_out, a.flags};
     if (code & kRouteOn) {
-        if (!(code & kRouteLive))
-            return;  // uniform: this pass's digit is the same for every key
+        if (!(code & kRouteLive)) {
+            // uniform: this pass's digit is the same for every key
+            if ((a.flags & RADIX_FLAG_COPIES) && route_m(code) == 0)
+                finish_copies(a.route, 0, a.n, KB, VB, (size_t)blockIdx.x * THREADS + threadIdx.x,
+                              (size_t)gridDim.x * THREADS);
+            return;
+        }
         route_pass(a.route, route_j(code), route_m(code), io);
     }
     if (tile >= a.tiles)
