@@ -17,6 +17,10 @@
  *     sorted, then runs are merged pairwise with doubling length;
  *   - below a fallback threshold (the paper's T_numpy) one workgroup sorts the
  *     whole array (the paper hands such arrays to the platform's library sort).
+ * With the automatic choice, arrays between one workgroup's size and some 4e5
+ * keys are sorted by splitters instead (blocks, then the buckets between sampled
+ * splitters), and a radix sort of 8-byte keys makes passes over the upper digits
+ * only where a sample says that these tell the keys apart.
  * The tunables of the paper's parameter vector (Sec. 3.2 and Sec. 4.2:
  * T_insertion, A_code, T_numpy) are fields of evosort_params, together with
  * the GPU's own knobs (digit width, tile shape).

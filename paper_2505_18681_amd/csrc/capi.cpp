@@ -147,11 +147,11 @@ constexpr int64_t kStatus32Limit = (int64_t)1 << 30;  // 32-bit look-back words 
 // Lengths the automatic choice sorts by splitters.  Below, one workgroup is
 // faster (int32 8192 keys 14.6 us against 19.4; int64 4096 15 / 23.6) or as
 // fast (argsort of float32 8192 keys 25.9 / 24.5).  Above, the radix sort is
-// (int32 4e5 keys 55 us against 45, 5e5 58 / 65; argsort of float32 2.6e5
-// 57 / 46, 4e5 61 / 68; int64 3e5 69 us with a prefix sort).  In between, us
-// per sort of the other routines and of this one: int32 16383 36 / 19.8,
-// 1e5 47 / 24.5; int64 16000 77 / 24.7, 5e4 67 / 26 (mergesort), 1.3e5 90 / 37;
-// float64 pairs 5e4 91 / 38.
+// (other routine / this one, us per sort: int32 3e5 keys 44.9 / 37.8, 4e5 47.0 /
+// 47.7, 5e5 50 / 65; argsort of float32 2.5e5 49.6 / 45.9; int64 2.6e5 68.8 /
+// 53.3, 3e5 the same).  In between: int32 16383 36 / 19.8, 1e5 39.5 / 24.3; int64
+// 16000 77 / 24.7, 5e4 67 / 26 (mergesort), 1e5 57.6 / 33.8; float64 pairs 5e4
+// 91 / 38.
 constexpr int64_t split_least(int key_bytes) { return key_bytes == 4 ? 8193 : 4097; }
 constexpr int64_t split_most(int key_bytes, int val_bytes)
 {

@@ -3,7 +3,7 @@
 // in order of their upper digits, keys of equal upper digits (a run) beside
 // each other in input order; here every run is put in order of the lower
 // digits, stably.  The plan takes this route only when a sample says that the
-// runs are short (radix_scan_kernel), but any run length is sorted:
+// runs are short (write_plan), but any run length is sorted:
 //
 //   radix_runs_kernel       a tile of keys with kRunMost keys on either side in
 //                           LDS; every key counts the larger keys of its run
