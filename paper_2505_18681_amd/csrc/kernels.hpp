@@ -187,6 +187,7 @@ constexpr uint32_t RADIX_FLAG_SKIP_KEYS = 2u;     // do not write keys (argsort,
 constexpr uint32_t RADIX_FLAG_WITHHOLD_T0 = 4u;   // debug: tile 0 never publishes
 constexpr uint32_t RADIX_FLAG_COPIES = 16u;       // last pass of a sort with no finishing launch: with no live pass,
                                                   // the copy to the output (finish_copies)
+constexpr uint32_t RADIX_FLAG_MAY_SKIP = 32u;     // a pass that a prefix sort may leave out: ask the plan first
 constexpr uint32_t RADIX_FLAG_PREFIX = 8u;        // status holds each tile's exclusive digit prefixes, computed
                                                   // before the pass: no publication, no look-back
 

@@ -124,3 +124,12 @@ def test_run_above_one_workgroup():
     """A run longer than one workgroup's sort holds (merged in pieces) and out of order in four places that the
     sample does not see."""
     _run_all(require_gpu(), _keys("strangers", 100_003), True, most=18_000)
+
+
+@pytest.mark.parametrize("name,prefix", [("uniform", True), ("one_top_byte", False)])
+@pytest.mark.parametrize("tiles", [511, 512])
+def test_passes_left_out_before_their_tickets(tiles, name, prefix):
+    """From 512 tiles on the lower passes read the plan before they take a ticket."""
+    es = require_gpu()
+    p = es.default_params(algo=es.ALGO_RADIX, block_threads=256, items_per_thread=8)
+    _run_all(es, _keys(name, tiles * 2048), prefix, params=p)
