@@ -150,7 +150,7 @@ hipError_t launch_class(const KeyDesc& kd, const SegBlockArgs& a, uint32_t max_s
             resident = 1024;  // any grid is correct; this only sizes the persistent launch
         }
     }
-    const uint32_t want = WAVE ? (max_segments + 3) / 4 : max_segments;
+    const uint32_t want = WAVE ? seg_wave_groups(max_segments) : max_segments;
     const uint32_t grid = want < (uint32_t)resident ? want : (uint32_t)resident;
     if (grid == 0)
         return hipSuccess;

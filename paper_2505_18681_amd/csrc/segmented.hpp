@@ -135,6 +135,9 @@ hipError_t launch_seg_classify(const SegClassifyArgs& a, hipStream_t s);
 hipError_t launch_seg_setup(const SegLargeArgs& a, uint32_t tile_keys, uint32_t grid, hipStream_t s);
 hipError_t launch_seg_histogram(const KeyDesc& kd, const SegHistArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_seg_scan(const SegLargeArgs& a, uint32_t grid, hipStream_t s);
+// Workgroups of four waves, one wave per segment (nseg is up to 2^32 - 2: no
+// rounding up in 32 bits).
+constexpr uint32_t seg_wave_groups(uint32_t segments) { return segments / 4 + (segments % 4 != 0 ? 1 : 0); }
 // One launch per class: persistent workgroups, for at most max_segments
 // segments and no more of them than fit on the device at once.
 hipError_t launch_seg_block_sort(const KeyDesc& kd, int val_bytes, int cls, const SegBlockArgs& a,
