@@ -133,7 +133,7 @@ def run_sort_bench(es, torch, dtype_name: str, n: int, steps: int, warmup: int, 
     # the plan the last radix sort left in its scratch: stages, and the first pass of a prefix sort (its last stage
     # is the run sort, not a pass); a pass left out is still launched, and exits
     stages, prefix = temp[24:26].tolist()
-    live_passes = stages - (1 if prefix else 0) if info["path_name"] == "radix" else 0
+    live_passes = stages - (1 if prefix else 0) if "radix_pass" in kernels else 0
 
     # cheap device-side sanity check of the last output (parity lives in tests/)
     if n > 1:
@@ -306,6 +306,13 @@ def run_tuned_bench(es, torch, n: int, seed: int, pop: int, generations: int, re
             "entries": out, "search_s": round(time.perf_counter() - t0, 1)}
 
 
+def route_name(info):
+    """What a call with plan `info` (and the scratch the library asks for) runs; radix: its tile."""
+    if info["split_blocks"]:
+        return "splitters"
+    return info["path_name"] if info["path_name"] != "radix" else [info["block_threads"], info["items_per_thread"]]
+
+
 def run_auto_table_bench(es, torch, seed: int, steps: int = 7):
     """Where the GA table the library compiles in replaces the hand-coded defaults of the automatic choice
     (A_code 0), the sort with the table's pick (default params), with the hand-coded default (A_code 4) and
@@ -349,8 +356,7 @@ def run_auto_table_bench(es, torch, seed: int, steps: int = 7):
         for (label, p), out in zip(cases, outs):
             info = es.plan(es.OP_SORT, es.dtype_code(keys.dtype), n, 0, p)
             res[label + "_ms"] = round(median_ms(keys, out, p), 4)
-            res[label + "_route"] = (info["path_name"] if info["path_name"] != "radix" else
-                                     [info["block_threads"], info["items_per_thread"]])
+            res[label + "_route"] = route_name(info)
         bits = [o.view(torch.int32 if o.element_size() == 4 else torch.int64) for o in outs]
         if not (torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2])):
             raise RuntimeError("table, hand-coded and closed-form sorts differ")
@@ -613,13 +619,13 @@ def run_routines_bench(es, torch, seed: int, n_merge: int = 100_000_000, steps: 
     keys = torch.from_numpy(workloads.uniform(np.int32, n_small, seed)).cuda()
     out = torch.empty_like(keys)
     p = es.default_params()
-    assert es.plan(es.OP_SORT, es.INT32, n_small, 0, p)["path_name"] == "small"
+    route = route_name(es.plan(es.OP_SORT, es.INT32, n_small, 0, p))
     temp = torch.empty(max(es.temp_bytes(es.OP_SORT, es.INT32, n_small, 0, p), 256), dtype=torch.uint8,
                        device="cuda")
     us = 1000 * timed(lambda: es.sort(keys, params=p, out=out, temp=temp), 200)
     if not bool((out[1:] >= out[:-1]).all().item()):
         raise RuntimeError("small-array output is not sorted")
-    small = {"workload": f"int32 uniform {n_small} keys (one workgroup), back-to-back calls on one stream",
+    small = {"workload": f"int32 uniform {n_small} keys (default parameters: {route}), back-to-back calls on one stream",
              "us_per_call": round(us, 2), "mkeys_per_s": round(n_small / us, 1), "bound": "latency"}
     return {"merge": merge, "small": small}
 

@@ -113,7 +113,8 @@ typedef enum evosort_op {
     EVOSORT_OP_ARGSORT = 2     /* keys in, permutation out, index of value_bytes (4 or 8) */
 } evosort_op;
 
-/* Routine a call takes (the branches of Sec. 4.3, Algorithm 6). */
+/* Routine a call takes (the branches of Sec. 4.3, Algorithm 6), unless the
+ * plan has split_blocks. */
 typedef enum evosort_path {
     EVOSORT_PATH_COPY = 0,  /* n <= 1: at most a copy */
     EVOSORT_PATH_SMALL = 1, /* n below the fallback threshold: one workgroup sorts all */
@@ -170,7 +171,7 @@ typedef struct evosort_params {
 
 /* What a call with the given arguments would do (host only; no GPU needed). */
 typedef struct evosort_plan_info {
-    int32_t path;             /* evosort_path */
+    int32_t path;             /* evosort_path: the branch's routine (see split_blocks) */
     uint32_t passes;          /* radix passes (0 unless path == RADIX) */
     uint32_t digit_bits;      /* effective d */
     uint32_t block_threads;   /* radix tile shape in effect */
@@ -179,9 +180,9 @@ typedef struct evosort_plan_info {
     uint64_t tile_keys;       /* keys per radix tile, or per mergesort block */
     uint64_t tiles;           /* radix tiles per pass, or mergesort blocks */
     uint32_t merge_rounds;    /* global merge rounds after the block sort (path == MERGE) */
-    uint32_t reserved;        /* with the automatic choice, the sorted blocks of a splitter sort,
-                                 which then runs instead of the routine of `path` (same result)
-                                 where the scratch is at least evosort_temp_bytes; else 0 */
+    uint32_t split_blocks;    /* not 0: a splitter sort of this many blocks runs instead of the
+                                 routine of `path` (same result), given a scratch of
+                                 evosort_temp_bytes */
     uint64_t merge_block_run; /* sorted run length after the mergesort block sort */
     uint64_t small_capacity;  /* largest n the one-workgroup sort takes for this dtype/op */
     uint64_t temp_bytes;      /* same as evosort_temp_bytes */

@@ -97,7 +97,7 @@ class PlanInfo(ctypes.Structure):
         ("tile_keys", ctypes.c_uint64),
         ("tiles", ctypes.c_uint64),
         ("merge_rounds", ctypes.c_uint32),
-        ("reserved", ctypes.c_uint32),
+        ("split_blocks", ctypes.c_uint32),
         ("merge_block_run", ctypes.c_uint64),
         ("small_capacity", ctypes.c_uint64),
         ("temp_bytes", ctypes.c_uint64),
@@ -239,9 +239,11 @@ def temp_bytes(op: int, dtype_code: int, n: int, value_bytes: int = 0, params: P
 
 
 def plan(op: int, dtype_code: int, n: int, value_bytes: int = 0, params: Params | None = None) -> dict:
+    """The fields of ``evosort_plan_info`` and ``path_name``, the name of the branch's routine.  Where ``split_blocks``
+    is not 0, a splitter sort of that many blocks runs instead of that routine."""
     info = PlanInfo()
     _check("evosort_plan", _lib.evosort_plan(op, dtype_code, n, value_bytes, _pp(params), ctypes.byref(info)))
-    d = {name: getattr(info, name) for name, _ in PlanInfo._fields_ if name != "reserved"}
+    d = {name: getattr(info, name) for name, _ in PlanInfo._fields_}
     d["path_name"] = PATH_NAMES.get(info.path, "?")
     return d
 

@@ -516,7 +516,7 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
                p.debug_flags == 0 && n >= split_least(kb) && n <= split_most(kb, vb);
     if (P->split) {
         P->sp = split_plan(n);
-        P->info.reserved = P->sp.blocks;
+        P->info.split_blocks = P->sp.blocks;
         size_t o = kAlign;
         P->off_split = o;
         o = align_up(o + (size_t)P->sp.buckets * 16);
