@@ -315,9 +315,10 @@ def route_name(info):
 
 def run_auto_table_bench(es, torch, seed: int, steps: int = 7):
     """Where the GA table the library compiles in replaces the hand-coded defaults of the automatic choice
-    (A_code 0), the sort with the table's pick (default params), with the hand-coded default (A_code 4) and
-    with the closed-form parameters, on uniform keys at each row's size class; median of `steps` event-timed
-    sorts after a quarter second of untimed ones, outputs checked identical."""
+    (A_code 0), the sort with the table's pick (the caller's own T_numpy, 0, which leaves the choice to the
+    table), with the hand-coded default (A_code 4), with the closed-form parameters and with default params, on
+    uniform keys at each row's size class; median of `steps` event-timed sorts after a quarter second of untimed
+    ones, outputs checked identical."""
     import numpy as np
 
     import workloads
@@ -349,17 +350,18 @@ def run_auto_table_bench(es, torch, seed: int, steps: int = 7):
             keys = torch.from_numpy(host.view(np.int32)).cuda().view(torch.uint32)
         else:
             keys = torch.from_numpy(host).cuda()
-        outs = [torch.empty_like(keys) for _ in range(3)]
-        cases = (("table", es.default_params()), ("hand_coded", es.default_params(algo=es.ALGO_RADIX)),
-                 ("closed_form", tuner.closed_form_params(es, name, n)))
+        outs = [torch.empty_like(keys) for _ in range(4)]
+        cases = (("table", es.default_params(fallback_threshold=0)),
+                 ("hand_coded", es.default_params(algo=es.ALGO_RADIX)),
+                 ("closed_form", tuner.closed_form_params(es, name, n)), ("default", es.default_params()))
         res = {"dtype": name, "n": n}
         for (label, p), out in zip(cases, outs):
             info = es.plan(es.OP_SORT, es.dtype_code(keys.dtype), n, 0, p)
             res[label + "_ms"] = round(median_ms(keys, out, p), 4)
             res[label + "_route"] = route_name(info)
         bits = [o.view(torch.int32 if o.element_size() == 4 else torch.int64) for o in outs]
-        if not (torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2])):
-            raise RuntimeError("table, hand-coded and closed-form sorts differ")
+        if not all(torch.equal(bits[0], b) for b in bits[1:]):
+            raise RuntimeError("table, hand-coded, closed-form and default sorts differ")
         res["table_speedup"] = round(res["hand_coded_ms"] / res["table_ms"], 3)
         entries.append(res)
         del keys, outs, bits, host

@@ -17,10 +17,11 @@
  *     sorted, then runs are merged pairwise with doubling length;
  *   - below a fallback threshold (the paper's T_numpy) one workgroup sorts the
  *     whole array (the paper hands such arrays to the platform's library sort).
- * With the automatic choice, arrays between one workgroup's size and some 4e5
- * keys are sorted by splitters instead (blocks, then the buckets between sampled
- * splitters), and a radix sort of 8-byte keys makes passes over the upper digits
- * only where a sample says that these tell the keys apart.
+ * With the automatic choice and default thresholds, arrays between one
+ * workgroup's size and some 4e5 keys are sorted by splitters instead (blocks, then
+ * the buckets between sampled splitters).  A radix sort of 8-byte keys makes
+ * passes over the upper digits only where a sample says that these tell the keys
+ * apart.
  * The tunables of the paper's parameter vector (Sec. 3.2 and Sec. 4.2:
  * T_insertion, A_code, T_numpy) are fields of evosort_params, together with
  * the GPU's own knobs (digit width, tile shape).
@@ -86,8 +87,10 @@ typedef enum evosort_dtype {
  * size, Sec. 6), except for keys-only sorts with no tile shape given whose key
  * type and length fall in a row of the GA tuner's table compiled into the
  * library (Sec. 4.2, Algorithm 2, run on an MI355X): there the row's routine,
- * the mergesort, is taken.  Other values are rejected with
- * EVOSORT_ERR_INVALID_ARG. */
+ * the mergesort, is taken.  With the default T_ins, T_numpy, digit width and no
+ * tile shape or debug switch, lengths up to some 4e5 keys are sorted by splitters
+ * instead of that routine (evosort_plan_info.split_blocks).  Other values are
+ * rejected with EVOSORT_ERR_INVALID_ARG. */
 typedef enum evosort_algo {
     EVOSORT_ALGO_AUTO = 0,
     EVOSORT_ALGO_MERGE = 3,
