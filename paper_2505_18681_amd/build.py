@@ -115,18 +115,28 @@ def _check_pass_kernels(usage: dict):
         raise RuntimeError("radix pass kernels lost occupancy or spill:\n  " + "\n  ".join(bad))
 
 
-def _check_no_scratch(usage: dict, what: str):
-    """No kernel of the unit uses scratch (spills or private arrays in memory)."""
-    bad = [f"{name}: {u['ScratchSize']} bytes of scratch per lane" for name, u in usage.items()
-           if u.get("ScratchSize", 0) > 0]
+def _check_scratch(usage: dict, what: str, spills: dict | None = None):
+    """No kernel of the unit uses scratch (spills or private arrays in memory), but for the ones in `spills` (name
+    pattern -> bytes per lane), which 1024 threads leave short of registers: those stay within what they have."""
+    bad = []
+    for name, u in usage.items():
+        most = max((b for pattern, b in (spills or {}).items() if re.search(pattern, name)), default=0)
+        if u.get("ScratchSize", 0) > most:
+            bad.append(f"{name}: {u['ScratchSize']} bytes of scratch per lane, {most} at most")
     if bad:
         raise RuntimeError(f"{what} kernels use scratch:\n  " + "\n  ".join(bad))
 
 
 # Units whose kernels' resource usage is checked at build time.
 CHECKED_UNITS = {"radix_inst.hip": _check_pass_kernels,
-                 "merge.hip": lambda usage: _check_no_scratch(usage, "mergesort"),
-                 "split_sort.hip": lambda usage: _check_no_scratch(usage, "splitter sort")}
+                 "merge.hip": lambda usage: _check_scratch(usage, "mergesort"),
+                 "small_sort.hip": lambda usage: _check_scratch(usage, "small-array"),
+                 "split_sort.hip": lambda usage: _check_scratch(usage, "splitter sort"),
+                 "radix_runs.hip": lambda usage: _check_scratch(usage, "run sort",
+                                                                {r"radix_long_runs_kernelILi8ELi0E": 36}),
+                 "seg_block.hip": lambda usage: _check_scratch(
+                     usage, "short segments'", {r"seg_block_sort_kernelILi4ELi0ELi16ELi16E": 60,
+                                                r"seg_block_sort_kernelILi\dELi\dELi16ELi8E": 12})}
 
 
 def _compile(unit, verbose, defines=()):
