@@ -1,8 +1,9 @@
 // One-workgroup LSD radix sort of up to THREADS * ITEMS keys held in
 // registers and LDS (Sec. 4, Algorithms 4 and 5 at workgroup scale: per-digit
 // counts, prefix sums, placement, with the paper's 8-bit digits).  Used for
-// the short segments of a batched sort and for the small-array branch of the
-// adaptive partition sort (Sec. 4.3, Algorithm 6).
+// the longest arrays of the small-array branch of the adaptive partition sort
+// (Sec. 4.3, Algorithm 6; the networks of wave_merge.hpp sort shorter ones) and
+// for the long runs of a prefix sort.
 //
 // HBM sees one read and one write per key (and value): every pass ranks the
 // keys stably with the wave64 lane-bucket rank of the device-wide pass,
@@ -34,7 +35,6 @@ struct BlockLsdLds {
     static constexpr size_t UNION_BYTES = HIST_BYTES > STAGE_BYTES ? HIST_BYTES : STAGE_BYTES;
     __attribute__((aligned(16))) unsigned char uni[UNION_BYTES];
     uint32_t wtot[WAVES];
-    uint32_t job;
 };
 
 // Where one sort reads and writes.  Values are read from vals_in, or are the

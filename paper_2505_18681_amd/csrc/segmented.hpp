@@ -35,22 +35,14 @@ namespace evosort {
 constexpr int kSegBits = 8;
 constexpr int kSegBins = 1 << kSegBits;
 
-// One-workgroup classes for records of rb = key bytes + value bytes; the
-// capacity of a class is threads * items, ascending.
-struct SegClass {
-    int threads;
-    int items;
-};
+// One-workgroup classes for records of rb = key bytes + value bytes: the
+// longest segment of each, ascending.
 constexpr int kSegMaxClasses = 4;
 constexpr int seg_class_count(int rb) { return rb == 4 ? 4 : 3; }
-constexpr SegClass seg_class(int rb, int c)
+constexpr int64_t seg_class_capacity(int rb, int c)
 {
-    return c == 0   ? SegClass{64, 8}
-           : c == 1 ? SegClass{256, 8}
-           : c == 2 ? (rb <= 8 ? SegClass{512, 16} : SegClass{512, 8})
-                    : SegClass{1024, 16};
+    return c == 0 ? 512 : c == 1 ? 2048 : c == 2 ? (rb <= 8 ? 8192 : 4096) : 16384;
 }
-constexpr int64_t seg_class_capacity(int rb, int c) { return (int64_t)seg_class(rb, c).threads * seg_class(rb, c).items; }
 constexpr int64_t seg_block_capacity(int rb) { return seg_class_capacity(rb, seg_class_count(rb) - 1); }
 
 // Bits of the device error word.

@@ -392,7 +392,10 @@ hipError_t launch(bool buckets, const KeyDesc& kd, const SplitArgs& a, hipStream
     case 1024:
         return launch_t<2>(buckets, kd, a, s);
     case 2048:
-        return launch_t<4>(buckets, kd, a, s);
+        // 1024 keys a block reach the 2^18 keys that these widths go to
+        if constexpr (EVOSORT_KB == 4 && EVOSORT_VB == 0)
+            return launch_t<4>(buckets, kd, a, s);
+        return hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;
     }
