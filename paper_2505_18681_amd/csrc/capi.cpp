@@ -512,8 +512,8 @@ evosort_status make_plan(int op, int dtype, int64_t n, uint32_t value_bytes, con
     }
     // The automatic choice with the default parameters: the splitter sort in the
     // range where it is faster than the routine of the branch (the table's rows
-    // among them: int64 2e4 and 5e4 keys, mergesort 67 us, splitters 26).  A
-    // caller's own T_numpy or T_ins decides as in Algorithm 6.
+    // among them: int64 5e4 keys, mergesort 67 us, splitters 26).  A caller's
+    // own T_numpy or T_ins decides as in Algorithm 6.
     P->split = force == FORCE_NONE && p.algo == EVOSORT_ALGO_AUTO && !p.block_threads && p.digit_bits == 8 &&
                p.insertion_threshold == kDefaultInsertion && p.fallback_threshold == (uint64_t)kSmallCapacity &&
                p.debug_flags == 0 && n >= split_least(kb) && n <= split_most(kb, vb);

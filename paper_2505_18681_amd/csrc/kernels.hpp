@@ -65,8 +65,8 @@ uint32_t radix_histogram_groups(int64_t n, uint32_t tiles);
 hipError_t launch_radix_histogram(const KeyDesc& kd, const void* keys, int64_t n, int bits, int passes,
                                   uint64_t* hist, const HistRows& out, const SampleArgs& sample, hipStream_t s);
 
-// The all-pass histogram of 8-bit digits (passes 4 or 8, counts into rows) that
-// also writes, for every tile of tile_keys keys, the tile's counts of the
+// The all-pass histogram of 8-bit digits of 4-byte keys (passes 4, counts into
+// rows) that also writes, for every tile of tile_keys keys, the tile's counts of the
 // pass-0 digits: counts[tile * 256 + digit], words of status_bytes (4 or 8).
 hipError_t launch_radix_histogram_tiles(const KeyDesc& kd, const void* keys, int64_t n, int passes,
                                         const HistRows& out, void* counts, int status_bytes, uint32_t tile_keys,

@@ -54,8 +54,8 @@ int histogram_grid(int64_t n)
     if (n <= (int64_t)1 << 23 && want > kComputeUnits)
         want = kComputeUnits;
     // up to 2^27 keys three per CU (1e7 int64 keys: the whole sort 364 us with
-    // 768, 384 with 256, 396 with 2441 workgroups; 2e8 keys 6.33 ms with 768,
-    // 6.30 with 4096)
+    // 768, 384 with 256, 396 with 2441 workgroups); above, the count decides
+    // nothing (2e8 keys 6.33 ms with 768, 6.30 with 4096)
     if (n <= (int64_t)1 << 27 && want > 3 * kComputeUnits)
         want = 3 * kComputeUnits;
     return (int)want;

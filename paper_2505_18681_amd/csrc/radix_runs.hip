@@ -83,9 +83,12 @@ __device__ __forceinline__ bool any_bit(const uint64_t* set, int lo, int hi)
     return false;
 }
 
-// Bound by HBM while the runs are short: the keys (and values) are read once,
-// the halo from cache, and written once, each within its run of the place it
-// was read from.  Two bit sets in LDS, made from one ballot per 64 keys, hold
+// The keys (and values) are read once, the halo from cache, and written once,
+// each within its run of the place it was read from.  Bound by latency: 239 to
+// 255 registers leave one workgroup of eight waves per CU, too few to cover its
+// loads and LDS steps (1e9 int64 keys 8.0 ms, 2.0 TB/s; 3e7 float64 pairs with
+// 8-byte values 400 us, 2.4 TB/s; 1e7 int64 argsort, which writes no keys, 83 us,
+// 2.9 TB/s; a radix pass 3.7-3.9, the copy 5.1).  Two bit sets in LDS, made from one ballot per 64 keys, hold
 // where a run starts and where a key is above the next of its run; a key finds
 // its run from the first and leaves its place alone when the second is empty
 // there (equal keys, keys in order), so that only runs out of order are
@@ -390,9 +393,9 @@ hipError_t EVOSORT_RUNS_NAME(EVOSORT_KB, EVOSORT_VB)(const KeyDesc& kd, const Ra
 {
     using U = typename KeyWord<EVOSORT_KB>::U;
     const OrderMap<U> om{(U)kd.flip, (U)kd.neg, (U)kd.desc};
-    // as many workgroups as the GPU holds at once (four per CU), each looping
-    // over its tiles: where there is nothing to do, a launch lasts longer the
-    // more workgroups it has
+    // four workgroups per CU at most, each looping over its tiles (one at a time
+    // is resident, see above): where there is nothing to do, a launch lasts
+    // longer the more workgroups it has
     const int64_t tiles = (a.n + kRunTile - 1) / kRunTile;
     const uint32_t grid = (uint32_t)(tiles < 1024 ? tiles : 1024);
     hipLaunchKernelGGL((radix_runs_kernel<EVOSORT_KB, EVOSORT_VB>), dim3(grid), dim3(kRunThreads), 0, s, a, om);

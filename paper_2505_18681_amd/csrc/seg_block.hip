@@ -5,6 +5,11 @@
 // with merge levels in LDS (wave_merge.hpp), so HBM sees one read and one write
 // per key.  Bound by the VALU work of the networks (1.8e3-key segments, uint32,
 // 1e8 keys in all: a one-workgroup LSD sort by 8-bit digits here took 1.09 ms).
+// Networks here also with values above 4096 records, where a single array goes
+// to the LSD sort (small_sort.hip): many workgroups at once are bound otherwise
+// than one alone.  Whole calls, LSD sort / networks, 3e7 int32 keys with 4-byte
+// values in segments of 4000 keys 911 / 768 us, 5000 778 / 829, 6000 684 / 709,
+// 8000 695 / 592 (8192 records are sorted from 4097 keys on).
 // Waves and workgroups take their class's segments at a fixed stride: taking
 // them from a ticket counter costs about 12 ns per segment, since atomics on one
 // word are performed one after the other (1e6 segments of 100 keys: 11.7 ms).
