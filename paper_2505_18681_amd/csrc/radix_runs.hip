@@ -86,9 +86,9 @@ __device__ __forceinline__ bool any_bit(const uint64_t* set, int lo, int hi)
 // The keys (and values) are read once, the halo from cache, and written once,
 // each within its run of the place it was read from.  Bound by latency: 239 to
 // 255 registers leave one workgroup of eight waves per CU, too few to cover its
-// loads and LDS steps (1e9 int64 keys 8.0 ms, 2.0 TB/s; 3e7 float64 pairs with
-// 8-byte values 400 us, 2.4 TB/s; 1e7 int64 argsort, which writes no keys, 83 us,
-// 2.9 TB/s; a radix pass 3.7-3.9, the copy 5.1).  Two bit sets in LDS, made from one ballot per 64 keys, hold
+// loads and LDS steps (1e9 int64 keys 8.0 ms, 2.0 TB/s; 3e7 float64 keys with
+// 8-byte values 0.26 ms, 3.7 TB/s; 1e7 int64 argsort with 10 copies of each key,
+// which writes no keys, 82 us, 2.9 TB/s; a radix pass 3.7-3.9, the copy 5.1).  Two bit sets in LDS, made from one ballot per 64 keys, hold
 // where a run starts and where a key is above the next of its run; a key finds
 // its run from the first and leaves its place alone when the second is empty
 // there (equal keys, keys in order), so that only runs out of order are
