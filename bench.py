@@ -763,7 +763,7 @@ def summarize_trace(trace_dir: str, kernel: str, skip: int, passes: int, bytes_p
         us = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
         per.setdefault(short_kernel_name(r["Kernel_Name"]), []).append(us)
     total = sum(sum(v) for v in per.values())
-    lines = [f"# {title}", "", "Command (from the repository root on the GPU box):", "", "```", command, "```", "",
+    lines = [f"# {title}", "", "Command (from the repository root):", "", "```", command, "```", "",
              "| kernel | calls | avg (us) | min (us) | max (us) | share |", "|---|---|---|---|---|---|"]
     for name, v in sorted(per.items(), key=lambda kv: -sum(kv[1])):
         lines.append(f"| `{name}` | {len(v)} | {sum(v) / len(v):.1f} | {min(v):.1f} | {max(v):.1f} | "
